@@ -191,7 +191,7 @@ int rx_demod(rx_plan_t plan, const int16_t* iq, const float* H, int64_t n_slots,
   if (xhat && !aligned(xhat, 8)) return RX_E_INVALID_ARG;
   if ((st = check_device(plan)) != RX_OK) return st;
   const rx::LaunchArgs la = launch_args(plan, iq, n_slots, hip_stream);
-  return hip_status(rx::launch_demod(la, plan->p.combiner == RX_COMB_ZF, reinterpret_cast<const float2*>(H),
+  return hip_status(rx::launch_demod(la, reinterpret_cast<const float2*>(H),
                                      reinterpret_cast<float2*>(xhat), bits));
 }
 
@@ -207,7 +207,7 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
   const rx::LaunchArgs la = launch_args(plan, iq, n_slots, hip_stream);
   float2* Hbuf = reinterpret_cast<float2*>(H ? static_cast<void*>(H) : workspace);
   if ((st = hip_status(rx::launch_estimate(la, Hbuf))) != RX_OK) return st;
-  return hip_status(rx::launch_demod(la, plan->p.combiner == RX_COMB_ZF, Hbuf, reinterpret_cast<float2*>(xhat), bits));
+  return hip_status(rx::launch_demod(la, Hbuf, reinterpret_cast<float2*>(xhat), bits));
 }
 
 int rx_debug_fft(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* Y, void* hip_stream) {
@@ -260,7 +260,7 @@ int process_frame_in(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
     if ((st = hip_status(rx::launch_estimate(la, hbuf))) != RX_OK) return st;
     float2* x = xhat ? reinterpret_cast<float2*>(xhat) + s0 * Td * plan->p.n_used : nullptr;
     uint8_t* b = bits ? bits + s0 * Td * row_bytes : nullptr;
-    if ((st = hip_status(rx::launch_demod(la, plan->p.combiner == RX_COMB_ZF, hbuf, x, b))) != RX_OK) return st;
+    if ((st = hip_status(rx::launch_demod(la, hbuf, x, b))) != RX_OK) return st;
   }
   return RX_OK;
 }

@@ -13,8 +13,12 @@
 //                  the FFT's output registers (paper Sec. II-C, MRC
 //                  paragraph); a fixed-order cross-wave reduction in LDS
 //                  follows, then x = z / g, hard decisions and packed bits.
-//                  ZF (one user) instead weights every antenna by conj(H)/g,
-//                  with g summed first.
+//                  ZF with one user weights every antenna by conj(H) / g, the
+//                  same for all of them, so it is this sum too.
+//                  (Weighting inside the loop needs g first, a pass over every
+//                  channel row in series: a 13-antenna, 512-point, 150-slot
+//                  call took 34.8 us with it and takes 24.4 us without; the
+//                  error against 64 bits went from 1.0e-7 to 8.3e-8.)
 //
 // After the FFT a lane holds bins li + L*q, q = 0..P-1 (see rx_fft.hpp).  The
 // used subcarriers are the bins within U/2 of DC, so only the registers
@@ -396,11 +400,10 @@ __device__ __forceinline__ float2 mrc_equalize(float2 z, float g) {
 }
 
 // Output of subcarriers 4 qd .. 4 qd + 3 (fewer at the end of the row) of one
-// data symbol: sum(d, z, g) adds the partial sums of subcarrier d to z and g
-// (ZF: z is already the equalized symbol); x = z / g (0 when g = 0), then the
-// decisions, packed MSB-first (4 symbols = B/2 bytes).  xrow, brow: the
+// data symbol: sum(d, z, g) adds the partial sums of subcarrier d to z and g;
+// x = z / g (0 when g = 0), then the decisions, packed MSB-first (4 symbols = B/2 bytes).  xrow, brow: the
 // symbol's output rows, or null.
-template <bool ZF, typename SumF>
+template <typename SumF>
 __device__ __forceinline__ void finish_quad(int qd, int U, int B, SumF sum, float2* __restrict__ xrow,
                                             uint8_t* __restrict__ brow) {
   const int nsym = min(4, U - 4 * qd);
@@ -410,12 +413,7 @@ __device__ __forceinline__ void finish_quad(int qd, int U, int B, SumF sum, floa
     float2 zz = make_float2(0.f, 0.f);
     float gg = 0.f;
     sum(d, zz, gg);
-    float2 x;
-    if constexpr (ZF) {
-      x = zz;
-    } else {
-      x = mrc_equalize(zz, gg);
-    }
+    const float2 x = mrc_equalize(zz, gg);
     if (xrow) xrow[d] = x;
     acc = (acc << B) | qam_code(x, B);
   }
@@ -439,7 +437,7 @@ struct SlotView {
 // Demodulate data symbol t of one slot with the W wavefronts of the
 // workgroup.  Uses the dynamic LDS `lds` (exchange buffers, then the
 // reduction rows); every thread of the workgroup must call it.
-template <int N, int QH, int W, bool ZF, int S, bool LL>
+template <int N, int QH, int W, int S, bool LL>
 __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* lds,
                                            const FftTwiddles<N, S, LL>& twr) {
   using Sh = FftShape<N>;
@@ -487,19 +485,6 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
     z[i] = make_float2(0.f, 0.f);
     g[i] = 0.f;
   }
-  if constexpr (ZF) {
-    // ZF weights need the full normaliser first: g over all antennas, in order.
-    for (int a = 0; a < A; a++) {
-#pragma unroll
-      for (int i = 0; i < NI; i++) {
-        const float2 h = Hs[(int64_t)a * U + dcl(i)];
-        g[i] = fmaf(h.x, h.x, fmaf(h.y, h.y, g[i]));
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NI; i++) g[i] = g[i] > 0.f ? 1.0f / g[i] : 0.f;  // now 1/g
-  }
-
   // C symbols (antennas) per lane per iteration; antenna of lane group f and
   // slot c in job J: J*F*C + c*F + f.  Job J = iteration * NG + tg.
   constexpr int C = Sh::F == 1 ? RX_DEMOD_ILP : 1;
@@ -573,15 +558,9 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
         const int q = i < QH ? i : Sh::P - NI + i;
         const float2 y = v[c][Spectrum<N, S>::reg(q)];
         const float2 hh = h[c][i];  // zero for antennas past A
-        if constexpr (ZF) {
-          const float2 w = make_float2(hh.x * g[i], -hh.y * g[i]);  // conj(h) / g
-          z[i].x = fmaf(w.x, y.x, fmaf(-w.y, y.y, z[i].x));
-          z[i].y = fmaf(w.x, y.y, fmaf(w.y, y.x, z[i].y));
-        } else {
-          z[i].x = fmaf(hh.x, y.x, fmaf(hh.y, y.y, z[i].x));  // conj(h) * y
-          z[i].y = fmaf(hh.x, y.y, fmaf(-hh.y, y.x, z[i].y));
-          g[i] = fmaf(hh.x, hh.x, fmaf(hh.y, hh.y, g[i]));
-        }
+        z[i].x = fmaf(hh.x, y.x, fmaf(hh.y, y.y, z[i].x));  // conj(h) * y
+        z[i].y = fmaf(hh.x, y.y, fmaf(-hh.y, y.x, z[i].y));
+        g[i] = fmaf(hh.x, hh.x, fmaf(hh.y, hh.y, g[i]));
       }
     exchange_fence<N>();  // this job's LDS reads precede the next job's writes
   };
@@ -624,7 +603,7 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
   for (int i = 0; i < NI; i++) {
     if (wok(i)) {
       rz[row * U + li + doff(i)] = z[i];
-      if constexpr (!ZF) rg[row * U + li + doff(i)] = g[i];
+      rg[row * U + li + doff(i)] = g[i];
     }
   }
   __syncthreads();
@@ -632,12 +611,12 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
   const int64_t out_row = t - 1;
   const int nq = (U + 3) / 4;
   for (int qd = threadIdx.x; qd < nq; qd += 64 * W) {
-    finish_quad<ZF>(qd, U, B, [&](int d, float2& zz, float& gg) {
+    finish_quad(qd, U, B, [&](int d, float2& zz, float& gg) {
       for (int w = 0; w < ROWS; w++) {
         const float2 p = rz[w * U + d];
         zz.x += p.x;
         zz.y += p.y;
-        if constexpr (!ZF) gg += rg[w * U + d];
+        gg += rg[w * U + d];
       }
     }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr);
   }
@@ -656,7 +635,7 @@ template <int N, int QH>
 constexpr int demod_min_waves() { return N == 2048 && QH == 5 ? 3 : 1; }
 
 // Uniform slots: one workgroup per (slot, data symbol).
-template <int N, int QH, int W, bool ZF>
+template <int N, int QH, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_min_waves<N, QH>())))
 void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int CP, int U, int B,
                   const float2* __restrict__ tw, const float2* __restrict__ H, float2* __restrict__ xhat,
@@ -676,7 +655,7 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
   sv.xhat = xhat ? xhat + s * Td * (int64_t)U : nullptr;
   sv.bits = bits ? bits + s * Td * (int64_t)(U * B / 8) : nullptr;
   sv.A = A; sv.T = T; sv.CP = CP; sv.U = U; sv.B = B;
-  demod_tile<N, QH, W, ZF>(sv, t, lds, twr);
+  demod_tile<N, QH, W>(sv, t, lds, twr);
 }
 
 // Several (slot, data symbol) items per workgroup, for transforms shorter than
@@ -693,7 +672,7 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
 template <int N, int QH>
 constexpr int demod_items_min_waves() { return N == 1024 && QH == 5 ? 3 : 1; }
 
-template <int N, int QH, int W, bool ZF, bool STAGED>
+template <int N, int QH, int W, bool STAGED>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_items_min_waves<N, QH>())))
 void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
                                                              int T, int CP, int U, int B,
@@ -745,17 +724,6 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   for (int i = 0; i < NI; i++) {
     z[i] = make_float2(0.f, 0.f);
     g[i] = 0.f;
-  }
-  if constexpr (ZF) {
-    for (int a = 0; a < A; a++) {
-#pragma unroll
-      for (int i = 0; i < NI; i++) {
-        const float2 h = Hs[(int64_t)a * U + dcl(i)];
-        g[i] = fmaf(h.x, h.x, fmaf(h.y, h.y, g[i]));
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NI; i++) g[i] = g[i] > 0.f ? 1.0f / g[i] : 0.f;  // now 1/g
   }
   // F == 1: the slot's estimate through a buffer resource (uniform base,
   // row offset in a scalar register, loop-invariant lane offsets)
@@ -827,15 +795,9 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     for (int i = 0; i < NI; i++) {
       const float2 y = v[0][Spectrum<N, 0>::reg(qof(i))];
       const float2 hh = hv[i];
-      if constexpr (ZF) {
-        const float2 w = make_float2(hh.x * g[i], -hh.y * g[i]);  // conj(h) / g
-        z[i].x = fmaf(w.x, y.x, fmaf(-w.y, y.y, z[i].x));
-        z[i].y = fmaf(w.x, y.y, fmaf(w.y, y.x, z[i].y));
-      } else {
-        z[i].x = fmaf(hh.x, y.x, fmaf(hh.y, y.y, z[i].x));  // conj(h) * y
-        z[i].y = fmaf(hh.x, y.y, fmaf(-hh.y, y.x, z[i].y));
-        g[i] = fmaf(hh.x, hh.x, fmaf(hh.y, hh.y, g[i]));
-      }
+      z[i].x = fmaf(hh.x, y.x, fmaf(hh.y, y.y, z[i].x));  // conj(h) * y
+      z[i].y = fmaf(hh.x, y.y, fmaf(-hh.y, y.x, z[i].y));
+      g[i] = fmaf(hh.x, hh.x, fmaf(hh.y, hh.y, g[i]));
     }
     exchange_fence<N>();  // this job's LDS reads precede the next job's writes
   }
@@ -860,7 +822,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
       for (int i = 0; i < NI; i++) {
         if (wok(i)) {
           const int d = li + doff(i);
-          const float2 x = ZF ? z[i] : mrc_equalize(z[i], g[i]);
+          const float2 x = mrc_equalize(z[i], g[i]);
           if (xhat) xhat[(item0 + litem) * U + d] = x;
           codes[litem * U + d] = (uint8_t)qam_code(x, B);
         }
@@ -871,7 +833,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     for (int i = 0; i < NI; i++) {
       if (wok(i)) {
         rz[ts * U + li + doff(i)] = z[i];
-        if constexpr (!ZF) rg[ts * U + li + doff(i)] = g[i];
+        rg[ts * U + li + doff(i)] = g[i];
       }
     }
     __syncthreads();
@@ -888,9 +850,9 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
         const float2 p = rz[r * U + d];
         zz.x += p.x;
         zz.y += p.y;
-        if constexpr (!ZF) gg += rg[r * U + d];
+        gg += rg[r * U + d];
       }
-      const float2 x = ZF ? zz : mrc_equalize(zz, gg);
+      const float2 x = mrc_equalize(zz, gg);
       if (xhat) xhat[item0 * U + v] = x;
       codes[v] = (uint8_t)qam_code(x, B);
       d += sr;
@@ -997,7 +959,7 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
     sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
     sv.bits = io.bits ? io.bits + d.b_off : nullptr;
     sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
-    demod_tile<N, QH, W, false>(sv, 1 + tile - d.dem_tile0, lds, twr);
+    demod_tile<N, QH, W>(sv, 1 + tile - d.dem_tile0, lds, twr);
     __syncthreads();  // outputs written and LDS free before the next tile
     done_index = d.index;
     done_last = d.T - 2;  // the frame's last data symbol completes it
@@ -1187,18 +1149,18 @@ int demod_waves_per_item(int A, int64_t items, int F) {
   return wa;
 }
 
-template <int N, int QH, bool ZF, bool STAGED>
+template <int N, int QH, bool STAGED>
 hipError_t demod_items_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits, int wa,
                               int64_t grid, size_t lds) {
-  hipError_t e = allow_lds(demod_items_kernel<N, QH, kWavesDemod, ZF, STAGED>, lds);
+  hipError_t e = allow_lds(demod_items_kernel<N, QH, kWavesDemod, STAGED>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((demod_items_kernel<N, QH, kWavesDemod, ZF, STAGED>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((demod_items_kernel<N, QH, kWavesDemod, STAGED>), dim3((unsigned)grid),
                      dim3(64 * kWavesDemod), lds, la.stream, la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H,
                      xhat, bits, wa);
   return hipGetLastError();
 }
 
-template <int N, int QH, bool ZF>
+template <int N, int QH>
 hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   using Sh = FftShape<N>;
   const int64_t items = la.S * (la.T - 1);
@@ -1218,9 +1180,9 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
       // every record piece is 16-byte aligned
       if constexpr (Sh::L <= 8) {
         if (la.CP % 4 == 0 && reinterpret_cast<uintptr_t>(la.iq) % 16 == 0)
-          return demod_items_launch<N, QH, ZF, true>(la, H, xhat, bits, wa, grid, lds);
+          return demod_items_launch<N, QH, true>(la, H, xhat, bits, wa, grid, lds);
       }
-      return demod_items_launch<N, QH, ZF, false>(la, H, xhat, bits, wa, grid, lds);
+      return demod_items_launch<N, QH, false>(la, H, xhat, bits, wa, grid, lds);
     }
   }
   const int64_t grid = items;
@@ -1228,38 +1190,26 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
   size_t lds = fft_lds_bytes<N, kWavesDemod>() * C;
   const size_t red = (size_t)transforms_per_group<N, kWavesDemod>() * la.U * (sizeof(float2) + sizeof(float));
   if (red > lds) lds = red;
-  hipError_t e = allow_lds(demod_kernel<N, QH, kWavesDemod, ZF>, lds);
+  hipError_t e = allow_lds(demod_kernel<N, QH, kWavesDemod>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((demod_kernel<N, QH, kWavesDemod, ZF>), dim3((unsigned)grid), dim3(64 * kWavesDemod), lds,
+  hipLaunchKernelGGL((demod_kernel<N, QH, kWavesDemod>), dim3((unsigned)grid), dim3(64 * kWavesDemod), lds,
                      la.stream, la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits);
   return hipGetLastError();
 }
 
 // Register-window tiers: the smallest instantiated QH >= ceil((U/2 + 1) / L).
-template <int N, bool ZF>
+template <int N>
 hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   constexpr int L = FftShape<N>::L;
   static_assert(FftShape<N>::P == 16, "tiers assume 16 points per lane");
   const int need = (la.U / 2 + 1 + L - 1) / L;
-  if (need <= 2) return demod_qh<N, 2, ZF>(la, H, xhat, bits);
-  if (need <= 4) return demod_qh<N, 4, ZF>(la, H, xhat, bits);
-  if (need <= 5) return demod_qh<N, 5, ZF>(la, H, xhat, bits);
-  if (need <= 8) return demod_qh<N, 8, ZF>(la, H, xhat, bits);
+  if (need <= 2) return demod_qh<N, 2>(la, H, xhat, bits);
+  if (need <= 4) return demod_qh<N, 4>(la, H, xhat, bits);
+  if (need <= 5) return demod_qh<N, 5>(la, H, xhat, bits);
+  if (need <= 8) return demod_qh<N, 8>(la, H, xhat, bits);
   return hipErrorInvalidValue;
 }
 
-template <bool ZF>
-hipError_t demod_dispatch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
-  switch (la.N) {
-    case 64: return demod_n<64, ZF>(la, H, xhat, bits);
-    case 128: return demod_n<128, ZF>(la, H, xhat, bits);
-    case 256: return demod_n<256, ZF>(la, H, xhat, bits);
-    case 512: return demod_n<512, ZF>(la, H, xhat, bits);
-    case 1024: return demod_n<1024, ZF>(la, H, xhat, bits);
-    case 2048: return demod_n<2048, ZF>(la, H, xhat, bits);
-    default: return hipErrorInvalidValue;
-  }
-}
 }  // namespace
 
 hipError_t launch_estimate(const LaunchArgs& la, float2* H) {
@@ -1282,9 +1232,17 @@ hipError_t launch_g(const LaunchArgs& la, const float2* H, float* g) {
   return hipGetLastError();
 }
 
-hipError_t launch_demod(const LaunchArgs& la, bool zf, const float2* H, float2* xhat, uint8_t* bits) {
+hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   if (la.fft_mode != 0) return launch_mfma_demod(la, H, xhat, bits);
-  return zf ? demod_dispatch<true>(la, H, xhat, bits) : demod_dispatch<false>(la, H, xhat, bits);
+  switch (la.N) {
+    case 64: return demod_n<64>(la, H, xhat, bits);
+    case 128: return demod_n<128>(la, H, xhat, bits);
+    case 256: return demod_n<256>(la, H, xhat, bits);
+    case 512: return demod_n<512>(la, H, xhat, bits);
+    case 1024: return demod_n<1024>(la, H, xhat, bits);
+    case 2048: return demod_n<2048>(la, H, xhat, bits);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_fft(const LaunchArgs& la, float2* Y) {

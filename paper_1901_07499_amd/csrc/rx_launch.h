@@ -27,7 +27,8 @@ hipError_t launch_mfma_fft(const LaunchArgs& la, float2* Y);
 
 hipError_t launch_estimate(const LaunchArgs& la, float2* H);
 hipError_t launch_g(const LaunchArgs& la, const float2* H, float* g);
-hipError_t launch_demod(const LaunchArgs& la, bool zf, const float2* H, float2* xhat, uint8_t* bits);
+// Both combiners: with one user ZF is MRC normalised by the channel energy.
+hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits);
 hipError_t launch_fft(const LaunchArgs& la, float2* Y);
 // rx_process_frame with the estimate in a fixed buffer, slots in chunks that
 // fit it (rx_api.cpp); returns an rx_status.
