@@ -86,6 +86,7 @@ rx::LaunchArgs launch_args(rx_plan_t plan, const int16_t* iq, int64_t S, void* s
   rx::LaunchArgs la;
   la.iq = reinterpret_cast<const uint32_t*>(iq);
   la.S = S;
+  la.S_call = S;
   la.A = plan->p.n_ant;
   la.N = plan->p.fft_len;
   la.CP = plan->p.cp_len;
@@ -205,9 +206,11 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
   if (!H && (!workspace || !aligned(workspace, 256))) return RX_E_INVALID_ARG;
   if ((st = check_device(plan)) != RX_OK) return st;
   const rx::LaunchArgs la = launch_args(plan, iq, n_slots, hip_stream);
-  float2* Hbuf = reinterpret_cast<float2*>(H ? static_cast<void*>(H) : workspace);
-  if ((st = hip_status(rx::launch_estimate(la, Hbuf))) != RX_OK) return st;
-  return hip_status(rx::launch_demod(la, Hbuf, reinterpret_cast<float2*>(xhat), bits));
+  float2* x2 = reinterpret_cast<float2*>(xhat);
+  if (!H) return hip_status(rx::launch_frame(la, static_cast<float2*>(workspace), x2, bits));
+  float2* H2 = reinterpret_cast<float2*>(H);
+  if ((st = hip_status(rx::launch_estimate(la, H2))) != RX_OK) return st;
+  return hip_status(rx::launch_demod(la, H2, x2, bits));
 }
 
 int rx_debug_fft(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* Y, void* hip_stream) {
@@ -256,11 +259,11 @@ int process_frame_in(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
   const int64_t row_bytes = (int64_t)plan->p.n_used * plan->p.bits_per_sym / 8;
   for (int64_t s0 = 0; s0 < n_slots; s0 += chunk) {
     const int64_t S = n_slots - s0 < chunk ? n_slots - s0 : chunk;
-    const rx::LaunchArgs la = launch_args(plan, iq + s0 * slot_iq, S, hip_stream);
-    if ((st = hip_status(rx::launch_estimate(la, hbuf))) != RX_OK) return st;
+    rx::LaunchArgs la = launch_args(plan, iq + s0 * slot_iq, S, hip_stream);
+    la.S_call = n_slots;
     float2* x = xhat ? reinterpret_cast<float2*>(xhat) + s0 * Td * plan->p.n_used : nullptr;
     uint8_t* b = bits ? bits + s0 * Td * row_bytes : nullptr;
-    if ((st = hip_status(rx::launch_demod(la, hbuf, x, b))) != RX_OK) return st;
+    if ((st = hip_status(rx::launch_frame(la, hbuf, x, b))) != RX_OK) return st;
   }
   return RX_OK;
 }

@@ -399,29 +399,71 @@ __device__ __forceinline__ float2 mrc_equalize(float2 z, float g) {
   return g > 0.f ? make_float2(z.x / g, z.y / g) : make_float2(0.f, 0.f);
 }
 
-// Output of subcarriers 4 qd .. 4 qd + 3 (fewer at the end of the row) of one
-// data symbol: sum(d, z, g) adds the partial sums of subcarrier d to z and g;
-// x = z / g (0 when g = 0), then the decisions, packed MSB-first (4 symbols = B/2 bytes).  xrow, brow: the
-// symbol's output rows, or null.
-template <typename SumF>
-__device__ __forceinline__ void finish_quad(int qd, int U, int B, SumF sum, float2* __restrict__ xrow,
-                                            uint8_t* __restrict__ brow) {
-  const int nsym = min(4, U - 4 * qd);
-  uint32_t acc = 0;  // bits of up to 4 symbols, MSB-first
-  for (int e = 0; e < nsym; e++) {
-    const int d = 4 * qd + e;
+// Sum of n partial sums get(w, z, g) in a fixed order: four chains of every
+// fourth term, then their sum.  Shorter chains round less than one (8 terms: an
+// 8-antenna call's error against 64 bits is 9.4e-8 summed one after another),
+// and their loads overlap.
+template <typename GetF>
+__device__ __forceinline__ void sum_in_chains(int n, GetF get, float2& z, float& g) {
+  float2 zc[4];
+  float gc[4];
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    zc[c] = make_float2(0.f, 0.f);
+    gc[c] = 0.f;
+  }
+  auto add = [&](int c, int w) {
+    float2 p;
+    float q;
+    get(w, p, q);
+    zc[c] = cadd(zc[c], p);
+    gc[c] += q;
+  };
+  int w = 0;
+  for (; w + 4 <= n; w += 4)
+#pragma unroll
+    for (int c = 0; c < 4; c++) add(c, w + c);
+#pragma unroll
+  for (int c = 0; c < 3; c++)
+    if (w + c < n) add(c, w + c);
+  z = cadd(cadd(zc[0], zc[1]), cadd(zc[2], zc[3]));
+  g = (gc[0] + gc[1]) + (gc[2] + gc[3]);
+}
+
+// Decision codes 4k .. 4k+3 (fewer at the end) of n consecutive subcarriers ->
+// bytes k B / 2 .. of out, by the whole workgroup.  Rows of U B bits are whole
+// bytes, so the rows of several symbols concatenate.
+template <int W>
+__device__ __forceinline__ void pack_codes(const uint8_t* codes, int n, int B, uint8_t* __restrict__ out) {
+  for (int k = threadIdx.x; 4 * k < n; k += 64 * W) {
+    const int m = min(4, n - 4 * k);
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(codes + 4 * k);
+    uint32_t acc = 0;
+    for (int e = 0; e < m; e++) acc = (acc << B) | ((w >> (8 * e)) & 0xffu);
+    const int nbytes = m * B / 8;
+    for (int byte = 0; byte < nbytes; byte++) out[k * (B / 2) + byte] = (uint8_t)(acc >> (m * B - 8 * (byte + 1)));
+  }
+}
+
+// Output of one data symbol by the whole workgroup of W wavefronts: sum(d, z,
+// g) gives the sums of subcarrier d; x = z / g (0 when g = 0), one thread per
+// subcarrier, then the decisions, whose codes meet in LDS (codes: U bytes and
+// 3 of slack, 4-byte aligned) and are packed MSB-first, one thread per four
+// (B/2 bytes).  xrow, brow: the symbol's output rows, or null.
+template <int W, typename SumF>
+__device__ __forceinline__ void finish_symbol(int U, int B, SumF sum, float2* __restrict__ xrow,
+                                              uint8_t* __restrict__ brow, uint8_t* codes) {
+  for (int d = threadIdx.x; d < U; d += 64 * W) {
     float2 zz = make_float2(0.f, 0.f);
     float gg = 0.f;
     sum(d, zz, gg);
     const float2 x = mrc_equalize(zz, gg);
     if (xrow) xrow[d] = x;
-    acc = (acc << B) | qam_code(x, B);
+    codes[d] = (uint8_t)qam_code(x, B);
   }
-  if (brow) {
-    const int nbits = nsym * B;  // a multiple of 8
-    uint8_t* o = brow + (qd * B) / 2;
-    for (int byte = 0; byte < nbits / 8; byte++) o[byte] = (uint8_t)(acc >> (nbits - 8 * (byte + 1)));
-  }
+  if (!brow) return;  // uniform
+  __syncthreads();
+  pack_codes<W>(codes, U, B, brow);
 }
 
 // One slot as seen by the per-tile routines (pointers already offset to the
@@ -608,18 +650,23 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
   }
   __syncthreads();
 
+  // rows past the antenna count hold zeros
   const int64_t out_row = t - 1;
-  const int nq = (U + 3) / 4;
-  for (int qd = threadIdx.x; qd < nq; qd += 64 * W) {
-    finish_quad(qd, U, B, [&](int d, float2& zz, float& gg) {
-      for (int w = 0; w < ROWS; w++) {
-        const float2 p = rz[w * U + d];
-        zz.x += p.x;
-        zz.y += p.y;
+  const int rows = min(ROWS, A);
+  finish_symbol<W>(U, B, [&](int d, float2& zz, float& gg) {
+    if constexpr (W == 8) {
+      sum_in_chains(rows, [&](int w, float2& p, float& q) {
+        p = rz[w * U + d];
+        q = rg[w * U + d];
+      }, zz, gg);
+    } else {
+      for (int w = 0; w < rows; w++) {
+        zz = cadd(zz, rz[w * U + d]);
         gg += rg[w * U + d];
       }
-    }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr);
-  }
+    }
+  }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
+  reinterpret_cast<uint8_t*>(rg + ROWS * U));
 }
 
 // Where the uniform demod keeps the last pass's twiddles: in VGPRs (no LDS
@@ -629,18 +676,18 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
 // faster; elsewhere in the LDS table.  The N = 2048 kernel with the 5-register
 // window needs a register budget of 3 wavefronts per SIMD to stay there (168
 // VGPRs; without the bound the compiler takes 169 and drops to 2).
-template <int N, int QH>
-constexpr bool demod_twiddles_in_lds() { return !((N == 1024 || N == 2048) && QH >= 5); }
-template <int N, int QH>
-constexpr int demod_min_waves() { return N == 2048 && QH == 5 ? 3 : 1; }
+template <int N, int QH, int W = 4>
+constexpr bool demod_twiddles_in_lds() { return W == 4 && !((N == 1024 || N == 2048) && QH >= 5); }
+template <int N, int QH, int W>
+constexpr int demod_min_waves() { return W == 8 ? 2 : N == 2048 && QH == 5 ? 3 : 1; }
 
 // Uniform slots: one workgroup per (slot, data symbol).
 template <int N, int QH, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_min_waves<N, QH>())))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_min_waves<N, QH, W>())))
 void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int CP, int U, int B,
                   const float2* __restrict__ tw, const float2* __restrict__ H, float2* __restrict__ xhat,
                   uint8_t* __restrict__ bits) {
-  using Tw = FftTwiddles<N, 0, demod_twiddles_in_lds<N, QH>()>;
+  using Tw = FftTwiddles<N, 0, demod_twiddles_in_lds<N, QH, W>()>;
   extern __shared__ float2 lds[];
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
   Tw twr;
@@ -660,26 +707,28 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
 
 // Several (slot, data symbol) items per workgroup, for transforms shorter than
 // a wavefront (F > 1 per wavefront) and for antenna counts too small to share
-// among the W wavefronts of one item.  A workgroup takes IPW = F * W / Wa
-// consecutive items: Wa wavefronts (1, 2 or 4) share an item's antennas
-// (wavefront w takes antennas w % Wa, w % Wa + Wa, ...), and transform slot f
-// of wavefront w serves item (w / Wa) * F + f of the workgroup, so one job of
-// a wavefront is one antenna of F items.  Each item's Wa partial sums meet in
-// LDS rows (row = transform slot, as in demod_tile); x-hat, decisions and
-// bits follow per item (paper Sec. II-C, MRC paragraph).
+// among the W wavefronts of one item.  Wa wavefronts (1, 2 or 4) and, in each,
+// Fa = 2^lfa of the F transform slots share an item's antennas; a workgroup
+// takes IPW = (W / Wa) (F / Fa) consecutive items: slot f of wavefront w serves
+// item (w / Wa) (F / Fa) + f / Fa and takes antennas (w % Wa) Fa + f % Fa,
+// + Wa Fa, ...  Each item's Wa Fa partial sums meet in LDS rows (row =
+// transform slot, as in demod_tile); x-hat, decisions and bits follow per item
+// (paper Sec. II-C, MRC paragraph).
 // The N = 1024 items kernel with the 5-register window is held at 3
 // wavefronts per SIMD (168 VGPRs; the compiler would otherwise take 169).
 template <int N, int QH>
 constexpr int demod_items_min_waves() { return N == 1024 && QH == 5 ? 3 : 1; }
 
-template <int N, int QH, int W, bool STAGED>
+// SPLIT: Fa > 1 is possible (calls too small to fill the chip; its antenna
+// bounds cost the large ones 3 to 6 %).
+template <int N, int QH, int W, bool STAGED, bool SPLIT>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_items_min_waves<N, QH>())))
 void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
                                                              int T, int CP, int U, int B,
                                                              const float2* __restrict__ tw,
                                                              const float2* __restrict__ H,
                                                              float2* __restrict__ xhat, uint8_t* __restrict__ bits,
-                                                             int Wa) {
+                                                             int Wa, int lfa_arg) {
   using Sh = FftShape<N>;
   static_assert(Sh::WPT == 1, "a transform within one wavefront");
   constexpr int NI = 2 * QH;
@@ -692,7 +741,10 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 
   const int Td = T - 1;
   const int64_t items = S * Td;
-  const int IPW = (W / Wa) * Sh::F;
+  static_assert(!SPLIT || Sh::F > 1, "slots of a wavefront to split");
+  const int lfa = SPLIT ? lfa_arg : 0;
+  const int Fa = 1 << lfa, FI = Sh::F >> lfa;  // slots per item, items per wavefront
+  const int IPW = (W / Wa) * FI;
   const int64_t item0 = xcd_remap(blockIdx.x, gridDim.x) * IPW;
   const int li = threadIdx.x % Sh::L, ts = threadIdx.x / Sh::L;
   const int f = ts % Sh::F;
@@ -700,7 +752,8 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   const int sub = wave % Wa;
   // item of this transform slot (uniform over the wavefront when F == 1); a
   // slot past the last item reads the last item's data and stores nothing
-  const int64_t item = item0 + (wave / Wa) * Sh::F + f;
+  const int64_t item = item0 + (wave / Wa) * FI + (f >> lfa);
+  const int fa = f & (Fa - 1);
   const int64_t ic = item < items ? item : items - 1;
   const int64_t s = ic / Td;
   const int t = 1 + (int)(ic - s * Td);
@@ -743,12 +796,14 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   // Direct loads would give each instruction L dwords of each of F records.
   using Sg = Staged<N>;
   const uint32_t* srec[STAGED ? Sg::kLoads : 1];
+  int sa[STAGED ? Sg::kLoads : 1];  // antenna offset of each piece's slot
   if constexpr (STAGED) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < Sg::kLoads; q++) {
       const int e = 4 * (64 * q + lane), fq = e / N;
-      const int64_t iq_ = item0 + (wave / Wa) * Sh::F + fq;
+      const int64_t iq_ = item0 + (wave / Wa) * FI + (fq >> lfa);
+      sa[q] = fq & (Fa - 1);
       const int64_t icq = iq_ < items ? iq_ : items - 1;
       const int64_t sq = icq / Td;
       const int tq = 1 + (int)(icq - sq * Td);
@@ -762,13 +817,17 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     if constexpr (STAGED) {
 #pragma unroll
       for (int q = 0; q < Sg::kLoads; q++)
-        nx4[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(srec[q] + (int64_t)aa * (N + CP)));
+        nx4[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
+            srec[q] + (int64_t)(SPLIT ? min(aa + sa[q], A - 1) : aa) * (N + CP)));
     } else {
-      load_symbol<N>(nxt, sym + (int64_t)aa * (N + CP), li, true);
+      load_symbol<N>(nxt, sym + (int64_t)(SPLIT ? min(aa + fa, A - 1) : aa) * (N + CP), li, true);
     }
   };
-  if (sub < A) request(sub);
-  for (int a = sub; a < A; a += Wa) {  // uniform over the wavefront
+  // antennas aa .. aa + Fa - 1 per job; a slot past the last antenna takes its
+  // samples and adds nothing (its channel row is taken as zero)
+  const int step = Wa << lfa;
+  if (sub << lfa < A) request(sub << lfa);
+  for (int aa = sub << lfa; aa < A; aa += step) {  // uniform over the wavefront
     float2 v[1][Sh::P];
     if constexpr (STAGED) {
       uint32_t raw[Sh::P];
@@ -780,16 +839,20 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     fft_first_pass<N, 1>(v, buf, li);
     float2 hv[NI];
     if constexpr (Sh::F == 1) {
-      const int so = a * (U * 8);
+      const int so = aa * (U * 8);
 #pragma unroll
       for (int i = 0; i < NI; i++)
         hv[i] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(hrs, hoff[i], so, 0));
     } else {
-      const float2* hrow = Hs + (int64_t)a * U;
+      const bool ok = !SPLIT || aa + fa < A;
+      const float2* hrow = Hs + (int64_t)(SPLIT ? min(aa + fa, A - 1) : aa) * U;
 #pragma unroll
-      for (int i = 0; i < NI; i++) hv[i] = hrow[dcl(i)];
+      for (int i = 0; i < NI; i++) {
+        const float2 hh = hrow[dcl(i)];
+        hv[i] = ok ? hh : make_float2(0.f, 0.f);
+      }
     }
-    if (a + Wa < A) request(a + Wa);
+    if (aa + step < A) request(aa + step);
     fft_rest<N, 1>(v, buf, li, twr);
 #pragma unroll
     for (int i = 0; i < NI; i++) {
@@ -804,9 +867,9 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 
   // The workgroup's items are consecutive, so their x-hat rows and bit rows
   // are contiguous.  x-hat and the decision codes (to LDS) come straight from
-  // the registers when one wavefront holds an item (Wa == 1); otherwise every
-  // transform slot's partial sums go to its LDS row and one thread per
-  // subcarrier sums the item's Wa rows in a fixed order.  Then one thread per
+  // the registers when one transform slot holds an item; otherwise every slot's
+  // partial sums go to its LDS row and one thread per subcarrier sums the
+  // item's Wa Fa rows in a fixed order.  Then one thread per
   // four codes packs the bits.
   constexpr int ROWS = W * Sh::F;
   const int nitems = (int)min((int64_t)IPW, items - item0);  // the last workgroup may hold fewer
@@ -815,7 +878,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   float2* rz = lds;                                      // [ROWS][U]
   float* rg = reinterpret_cast<float*>(lds + ROWS * U);  // [ROWS][U]
   uint8_t* codes = reinterpret_cast<uint8_t*>(rg + ROWS * U);  // [nsub] (+ 4 bytes of slack)
-  if (Wa == 1) {
+  if (step == 1) {
     const int litem = wave * Sh::F + f;
     if (litem < nitems) {
 #pragma unroll
@@ -842,15 +905,22 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     const int sq = kStride / U, sr = kStride - sq * U;
     int litem = threadIdx.x / U, d = threadIdx.x - litem * U;
     for (int v = threadIdx.x; v < nsub; v += kStride) {
-      const int row0 = (litem / Sh::F) * Wa * Sh::F + litem % Sh::F;  // row of wavefront sub 0
+      const int lf = __builtin_ctz(Sh::F) - lfa;  // log2 of the items per wavefront
+      const int row0 = (litem >> lf) * Wa * Sh::F + ((litem & (FI - 1)) << lfa);  // wavefront sub 0, slot 0
       float2 zz = make_float2(0.f, 0.f);
       float gg = 0.f;
-      for (int k = 0; k < Wa; k++) {
-        const int r = row0 + k * Sh::F;
-        const float2 p = rz[r * U + d];
-        zz.x += p.x;
-        zz.y += p.y;
-        gg += rg[r * U + d];
+      if constexpr (SPLIT) {
+        sum_in_chains(step, [&](int k, float2& p, float& q) {
+          const int r = (row0 + (k >> lfa) * Sh::F + (k & (Fa - 1))) * U + d;
+          p = rz[r];
+          q = rg[r];
+        }, zz, gg);
+      } else {
+        for (int k = 0; k < Wa; k++) {
+          const int r = (row0 + k * Sh::F) * U + d;
+          zz = cadd(zz, rz[r]);
+          gg += rg[r];
+        }
       }
       const float2 x = mrc_equalize(zz, gg);
       if (xhat) xhat[item0 * U + v] = x;
@@ -865,19 +935,143 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   }
   if (bits) {
     __syncthreads();
-    // codes 4k .. 4k+3 (fewer at the end) -> bytes k B / 2 .. of the bit rows
-    // (every row is a whole number of bytes, so the rows concatenate)
-    uint8_t* out = bits + item0 * (int64_t)(U * B / 8);
-    for (int k = threadIdx.x; 4 * k < nsub; k += 64 * W) {
-      const int n = min(4, nsub - 4 * k);
-      const uint32_t w = *reinterpret_cast<const uint32_t*>(codes + 4 * k);
-      uint32_t acc = 0;
-      for (int e = 0; e < n; e++) acc = (acc << B) | ((w >> (8 * e)) & 0xffu);
-      const int nbytes = n * B / 8;
-      for (int byte = 0; byte < nbytes; byte++)
-        out[k * (B / 2) + byte] = (uint8_t)(acc >> (n * B - 8 * (byte + 1)));
+    pack_codes<W>(codes, nsub, B, bits + item0 * (int64_t)(U * B / 8));
+  }
+}
+
+// ------------------------------------------------------------------ small calls
+// The whole path of few items in one kernel: workgroup = (slot, data symbol,
+// one of NB groups of the antennas).  A transform takes the pilot symbol of its
+// antenna, keeps the LS estimate of the window's subcarriers in registers (the
+// products the estimate kernel stores) and goes on to the antenna's data
+// symbol, so no estimate goes through memory and no second kernel waits for
+// it; the pilot's transform is repeated for every data symbol, on compute
+// units that would idle.  With NB > 1 the groups' sums go to zp, gp and
+// small_finish_kernel adds them in group order.
+template <int N, int QH, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void small_kernel(
+    const uint32_t* __restrict__ iq, int A, int T, int CP, int U, int B, const float2* __restrict__ tw,
+    const float2* __restrict__ pf, float2* __restrict__ xhat, uint8_t* __restrict__ bits, int NB,
+    float2* __restrict__ zp, float* __restrict__ gp) {
+  using Sh = FftShape<N>;
+  using El = EstLane<N, QH>;
+  constexpr int NI = El::NI, TPW = transforms_per_group<N, W>();
+  extern __shared__ float2 lds[];
+  const int Td = T - 1;
+  const int64_t item = blockIdx.x / NB;
+  const int b = blockIdx.x % NB;
+  const int64_t s = item / Td;
+  const int t = 1 + (int)(item - s * Td);
+  const int a0 = (int)((int64_t)A * b / NB), na = (int)((int64_t)A * (b + 1) / NB) - a0;
+  const int li = threadIdx.x % Sh::L, ts = threadIdx.x / Sh::L;
+  const uint32_t* pilot = iq + (s * T * A + a0) * (int64_t)(N + CP) + CP;
+  const int64_t to_data = (int64_t)t * A * (N + CP);
+  // a transform past the group's antennas takes the last one's samples and
+  // adds nothing
+  auto rec = [&](int k) { return pilot + (int64_t)min(k, na - 1) * (N + CP); };
+  uint32_t nxt[Sh::P];
+  load_symbol<N>(nxt, rec(ts), li, true);
+  El el;
+  el.init(li, U, pf);
+  // last-pass twiddles in the LDS table where the widest window needs the
+  // registers
+  using Tw = FftTwiddles<N, 0, QH == 8>;
+  __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
+  Tw twr;
+  tile_setup(twr, twtab, tw);
+  float2* const buf[1] = {lds + ts * Lds<N>::kSlot};
+  float2 z[NI];
+  float g[NI];
+#pragma unroll
+  for (int i = 0; i < NI; i++) {
+    z[i] = make_float2(0.f, 0.f);
+    g[i] = 0.f;
+  }
+  // first antenna of whoever shares an exchange fence: transforms within a
+  // wavefront end with their wavefront's antennas, wavefront pairs together
+  const int lead = Sh::WPT > 1 ? 0 : ts - ts % Sh::F;
+  // Even steps transform the pilot symbol of antenna k, odd ones its data
+  // symbol, by the same code: a call this short waits for instruction fetches
+  // too, and with two copies of the transform 128 antennas x 2048 points, one
+  // slot, took 37.0 us where it takes 30.8.
+  float2 h[NI];
+#pragma unroll 1
+  for (int k0 = 0, odd = 0; k0 + lead < na; k0 += odd ? TPW : 0, odd ^= 1) {
+    const int k = k0 + ts;
+    float2 v[1][Sh::P];
+    unpack_symbol<N>(v[0], nxt);
+    if (!odd) load_symbol<N>(nxt, rec(k) + to_data, li, true);
+    else if (k0 + TPW + lead < na) load_symbol<N>(nxt, rec(k + TPW), li, true);
+    fft_in_regs<N, 1>(v, buf, li, twr);
+    if (!odd) {
+#pragma unroll
+      for (int i = 0; i < NI; i++) {
+        const float2 y = cmul(v[0][Spectrum<N>::reg(El::qof(i))], el.pq[i]);
+        h[i] = k < na ? y : make_float2(0.f, 0.f);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; i++) {
+        const float2 y = v[0][Spectrum<N>::reg(El::qof(i))];
+        z[i].x = fmaf(h[i].x, y.x, fmaf(h[i].y, y.y, z[i].x));  // conj(h) * y
+        z[i].y = fmaf(h[i].x, y.y, fmaf(-h[i].y, y.x, z[i].y));
+        g[i] = fmaf(h[i].x, h[i].x, fmaf(h[i].y, h[i].y, g[i]));
+      }
+    }
+    exchange_fence<N>();
+  }
+  // rows of the group's antennas, summed in order (as in demod_tile)
+  const int rows = min(TPW, na);
+  __syncthreads();
+  float2* rz = lds;                                      // [rows][U]
+  float* rg = reinterpret_cast<float*>(lds + rows * U);  // [rows][U]
+  if (ts < rows) {
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+      if (el.dq[i] >= 0) {
+        rz[ts * U + el.dq[i]] = z[i];
+        rg[ts * U + el.dq[i]] = g[i];
+      }
+  }
+  __syncthreads();
+  auto sum = [&](int d, float2& zz, float& gg) {
+    sum_in_chains(rows, [&](int w, float2& p, float& q) {
+      p = rz[w * U + d];
+      q = rg[w * U + d];
+    }, zz, gg);
+  };
+  if (NB == 1) {
+    finish_symbol<W>(U, B, sum, xhat ? xhat + item * U : nullptr,
+                     bits ? bits + item * (int64_t)(U * B / 8) : nullptr, reinterpret_cast<uint8_t*>(rg + rows * U));
+  } else {
+    for (int d = threadIdx.x; d < U; d += 64 * W) {
+      float2 zz = make_float2(0.f, 0.f);
+      float gg = 0.f;
+      sum(d, zz, gg);
+      zp[(item * NB + b) * U + d] = zz;
+      if (t == 1) gp[(s * NB + b) * U + d] = gg;
     }
   }
+}
+
+// Sums of the NB antenna groups, then the outputs: workgroup = (item, 256 of
+// its subcarriers), one per thread, so a few items still spread over the chip.
+constexpr int kWavesFinish = 4;
+__global__ __launch_bounds__(64 * kWavesFinish) void small_finish_kernel(const float2* __restrict__ zp,
+                                                                        const float* __restrict__ gp, int NB, int Td,
+                                                                        int U, int B, float2* __restrict__ xhat,
+                                                                        uint8_t* __restrict__ bits) {
+  constexpr int kSeg = 64 * kWavesFinish;
+  __shared__ uint32_t codes[kSeg / 4 + 1];
+  const int segs = (U + kSeg - 1) / kSeg, d0 = blockIdx.x % segs * kSeg;
+  const int64_t item = blockIdx.x / segs, s = item / Td;
+  finish_symbol<kWavesFinish>(min(kSeg, U - d0), B, [&](int d, float2& zz, float& gg) {
+    sum_in_chains(NB, [&](int b, float2& p, float& q) {
+      p = zp[(item * NB + b) * U + d0 + d];
+      q = gp[(s * NB + b) * U + d0 + d];
+    }, zz, gg);
+  }, xhat ? xhat + item * U + d0 : nullptr, bits ? bits + (item * U + d0) * B / 8 : nullptr,
+  reinterpret_cast<uint8_t*>(codes));
 }
 
 // ------------------------------------------------------------------ batches
@@ -1139,6 +1333,8 @@ hipError_t fft_n(const LaunchArgs& la, float2* Y) {
   return hipGetLastError();
 }
 
+constexpr int kFillWaves = 1024;
+
 // Wavefronts per item of demod_items_kernel: every wavefront takes at least
 // one antenna, and an item's antennas spread over fewer wavefronts (at least 8
 // per wavefront) while the grid still has many wavefronts per resident slot.
@@ -1149,26 +1345,69 @@ int demod_waves_per_item(int A, int64_t items, int F) {
   return wa;
 }
 
-template <int N, int QH, bool STAGED>
-hipError_t demod_items_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits, int wa,
+// Transform slots of a wavefront per item, log2: one if the grid then has a
+// wavefront per SIMD (1024), else more until it has, or until each slot has
+// one antenna.  (100 antennas, 128 points, 72 slots: 43.5 us with one slot, 25.1
+// with this rule; a target of 2048 wavefronts took 31.3, of 4096 57.3 against
+// 41.5 at 150 slots: the split loses where an item's antennas end mid-job.)
+int demod_slots_log2(int A, int64_t items, int F, int wa) {
+  int l = 0;
+  while ((1 << l) < F && (wa << l) < A && items * (wa << l) / F < kFillWaves) l++;
+  return l;
+}
+
+template <int N, int QH, bool STAGED, bool SPLIT>
+hipError_t demod_items_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits, int wa, int lfa,
                               int64_t grid, size_t lds) {
-  hipError_t e = allow_lds(demod_items_kernel<N, QH, kWavesDemod, STAGED>, lds);
+  hipError_t e = allow_lds(demod_items_kernel<N, QH, kWavesDemod, STAGED, SPLIT>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((demod_items_kernel<N, QH, kWavesDemod, STAGED>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((demod_items_kernel<N, QH, kWavesDemod, STAGED, SPLIT>), dim3((unsigned)grid),
                      dim3(64 * kWavesDemod), lds, la.stream, la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H,
-                     xhat, bits, wa);
+                     xhat, bits, wa, lfa);
   return hipGetLastError();
 }
+
+// LDS of a kernel that sums rows of z and g per subcarrier and packs decision
+// codes (with slack for the packing's last 4-byte read), or exchanges.
+size_t rows_lds(size_t exchange, int rows, int U) {
+  const size_t red = (size_t)rows * U * (sizeof(float2) + sizeof(float)) + U + 4;
+  return red > exchange ? red : exchange;
+}
+
+// demod_kernel with W wavefronts.
+template <int N, int QH, int W>
+hipError_t demod_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
+  const size_t lds = rows_lds(fft_lds_bytes<N, W>(), transforms_per_group<N, W>(), la.U);
+  hipError_t e = allow_lds(demod_kernel<N, QH, W>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((demod_kernel<N, QH, W>), dim3((unsigned)(la.S * (la.T - 1))), dim3(64 * W), lds, la.stream,
+                     la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits);
+  return hipGetLastError();
+}
+
+// Items (slot, data symbol) up to which a call is small: one 8-wavefront
+// workgroup per item then still fits the compute units side by side, two
+// wavefronts per SIMD, and an item's antennas go through twice as fast as with
+// four wavefronts.  64 antennas, 1024 points, 18 slots (234 items): 38.1 us with
+// 4 wavefronts, 31.5 with 8; 128 x 2048, 18 slots: 168 and 136 us; at 24 slots
+// (312 items) a second round of workgroups would start, and 4 wavefronts, two
+// to three workgroups per compute unit, take 45.6 us.
+constexpr int kSmallItems = 256;
+constexpr int kWavesSmall = 8;
 
 template <int N, int QH>
 hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   using Sh = FftShape<N>;
   const int64_t items = la.S * (la.T - 1);
+  // (the rule looks at the whole call's slots: a call that goes through in
+  // chunks sums in one order)
+  if (la.S_call * (la.T - 1) <= kSmallItems) return demod_launch<N, QH, kWavesSmall>(la, H, xhat, bits);
   if constexpr (Sh::WPT == 1) {
-    const int wa = demod_waves_per_item(la.A, items, Sh::F);
+    const int wa = demod_waves_per_item(la.A, la.S_call * (la.T - 1), Sh::F);
     if (Sh::F > 1 || wa < kWavesDemod) {
       // several items per workgroup
-      const int ipw = (kWavesDemod / wa) * Sh::F;
+      const int lfa = demod_slots_log2(la.A, la.S_call * (la.T - 1), Sh::F, wa);
+      const int ipw = (kWavesDemod / wa) * (Sh::F >> lfa);
       const int64_t grid = (items + ipw - 1) / ipw;
       size_t lds = fft_lds_bytes<N, kWavesDemod>();
       // reduction rows (z, g) and one decision code per subcarrier, with 4
@@ -1178,23 +1417,19 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
       if (red > lds) lds = red;
       // staged 16-byte sample loads for transforms of at most 8 lanes when
       // every record piece is 16-byte aligned
+      const bool staged = Sh::L <= 8 && la.CP % 4 == 0 && reinterpret_cast<uintptr_t>(la.iq) % 16 == 0;
       if constexpr (Sh::L <= 8) {
-        if (la.CP % 4 == 0 && reinterpret_cast<uintptr_t>(la.iq) % 16 == 0)
-          return demod_items_launch<N, QH, true>(la, H, xhat, bits, wa, grid, lds);
+        if (staged)
+          return lfa ? demod_items_launch<N, QH, true, true>(la, H, xhat, bits, wa, lfa, grid, lds)
+                     : demod_items_launch<N, QH, true, false>(la, H, xhat, bits, wa, lfa, grid, lds);
       }
-      return demod_items_launch<N, QH, false>(la, H, xhat, bits, wa, grid, lds);
+      if constexpr (Sh::F > 1) {
+        if (lfa) return demod_items_launch<N, QH, false, true>(la, H, xhat, bits, wa, lfa, grid, lds);
+      }
+      return demod_items_launch<N, QH, false, false>(la, H, xhat, bits, wa, lfa, grid, lds);
     }
   }
-  const int64_t grid = items;
-  constexpr int C = Sh::F == 1 ? RX_DEMOD_ILP : 1;
-  size_t lds = fft_lds_bytes<N, kWavesDemod>() * C;
-  const size_t red = (size_t)transforms_per_group<N, kWavesDemod>() * la.U * (sizeof(float2) + sizeof(float));
-  if (red > lds) lds = red;
-  hipError_t e = allow_lds(demod_kernel<N, QH, kWavesDemod>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((demod_kernel<N, QH, kWavesDemod>), dim3((unsigned)grid), dim3(64 * kWavesDemod), lds,
-                     la.stream, la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits);
-  return hipGetLastError();
+  return demod_launch<N, QH, kWavesDemod>(la, H, xhat, bits);
 }
 
 // Register-window tiers: the smallest instantiated QH >= ceil((U/2 + 1) / L).
@@ -1243,6 +1478,75 @@ hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uin
     case 2048: return demod_n<2048>(la, H, xhat, bits);
     default: return hipErrorInvalidValue;
   }
+}
+
+namespace {
+template <int N, int QH>
+hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits) {
+  constexpr int W = kWavesSmall, TPW = transforms_per_group<N, W>();
+  const int64_t items = la.S * (la.T - 1);
+  const int na = (la.A + NB - 1) / NB;
+  const size_t lds = rows_lds(fft_lds_bytes<N, W>(), na < TPW ? na : TPW, la.U);
+  float2* zp = scratch;                                                  // [items][NB][U]
+  float* gp = reinterpret_cast<float*>(scratch + items * NB * la.U);  // [S][NB][U]
+  hipError_t e = allow_lds(small_kernel<N, QH, W>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((small_kernel<N, QH, W>), dim3((unsigned)(items * NB)), dim3(64 * W), lds, la.stream, la.iq,
+                     la.A, la.T, la.CP, la.U, la.B, la.tw, la.pf, xhat, bits, NB, zp, gp);
+  if ((e = hipGetLastError()) != hipSuccess || NB == 1) return e;
+  const int segs = (la.U + 64 * kWavesFinish - 1) / (64 * kWavesFinish);
+  hipLaunchKernelGGL(small_finish_kernel, dim3((unsigned)(items * segs)), dim3(64 * kWavesFinish), 0, la.stream,
+                     (const float2*)zp, (const float*)gp, NB, la.T - 1, la.U, la.B, xhat, bits);
+  return hipGetLastError();
+}
+
+template <int N>
+hipError_t small_n(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits) {
+  constexpr int L = FftShape<N>::L;
+  const int need = (la.U / 2 + 1 + L - 1) / L;
+  if (need <= 2) return small_launch<N, 2>(la, NB, scratch, xhat, bits);
+  if (need <= 5) return small_launch<N, 5>(la, NB, scratch, xhat, bits);
+  if (need <= 8) return small_launch<N, 8>(la, NB, scratch, xhat, bits);
+  return hipErrorInvalidValue;
+}
+}  // namespace
+
+// Antenna groups per item of the one-kernel path (0: not for this call).  It
+// costs two transforms per antenna where the two kernels cost one, and saves
+// the estimate kernel (about the time of three transforms in a row); several
+// groups shorten the row of transforms but add the finishing kernel (about
+// two).  The groups' sums share the A U 8 bytes per slot that the estimate
+// would have taken.  One slot, this path against the two kernels with 8
+// wavefronts (and with 4): 8 antennas x 64 points 8.1 us against 10.8 (11.8),
+// 64 x 1024 16.2 against 25.1 (33.6), 128 x 2048 30.8 against 114 (155);
+// towards the line they meet: 64 x 1024, 8 slots, 25.1 against 27.2.
+int small_groups(const LaunchArgs& la) {
+  const int64_t Td = la.T - 1, items = la.S_call * Td;
+  if (la.fft_mode != 0 || la.ps > 1 || items > kSmallItems) return 0;
+  const int per_wg = kWavesSmall * 1024 / la.N;  // transforms of a workgroup side by side
+  const int most = (la.A + per_wg - 1) / per_wg;
+  int nb = (int)(8 * (int64_t)la.A / (8 * Td + 4));
+  if (nb > most) nb = most;
+  if (nb > kSmallItems / items) nb = (int)(kSmallItems / items);
+  if (nb < 1) nb = 1;
+  const int rounds = ((la.A + nb - 1) / nb + per_wg - 1) / per_wg;
+  return 2 * rounds + (nb > 1 ? 2 : 0) < most + 3 ? nb : 0;
+}
+
+hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits) {
+  if (const int nb = small_groups(la)) {
+    switch (la.N) {
+      case 64: return small_n<64>(la, nb, scratch, xhat, bits);
+      case 128: return small_n<128>(la, nb, scratch, xhat, bits);
+      case 256: return small_n<256>(la, nb, scratch, xhat, bits);
+      case 512: return small_n<512>(la, nb, scratch, xhat, bits);
+      case 1024: return small_n<1024>(la, nb, scratch, xhat, bits);
+      case 2048: return small_n<2048>(la, nb, scratch, xhat, bits);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  const hipError_t e = launch_estimate(la, scratch);
+  return e != hipSuccess ? e : launch_demod(la, scratch, xhat, bits);
 }
 
 hipError_t launch_fft(const LaunchArgs& la, float2* Y) {
@@ -1295,7 +1599,8 @@ bool dem_pick(int max_u, int demod_waves, BatchKernel& dem) {
   if (!ok) return false;
   // LDS of the demod tile: exchange buffers, or the reduction rows if larger
   dem.lds_fft = (size_t)tpw<N>(demod_waves) * Lds<N>::kSlot * sizeof(float2);
-  dem.lds_per_u = (size_t)tpw<N>(demod_waves) * (sizeof(float2) + sizeof(float));
+  // and the decision codes (a byte each; 2 covers the packing's 4-byte reads)
+  dem.lds_per_u = (size_t)tpw<N>(demod_waves) * (sizeof(float2) + sizeof(float)) + 2;
   dem.ants_per_tile = 0;
   return true;
 }

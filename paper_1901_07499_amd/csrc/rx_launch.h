@@ -11,7 +11,8 @@ namespace rx {
 
 struct LaunchArgs {
   const uint32_t* iq;  // one dword per complex int16 sample, [S][T][A][CP+N]
-  int64_t S;
+  int64_t S;       // slots of this launch
+  int64_t S_call;  // and of the call it is part of (the kernel choice goes by these)
   int A, N, CP, U, T, B;
   const float2* tw;    // tw[k] = exp(-2 pi i k / N), k < N
   const float2* pf;    // pf[d] = conj(Xp[d]) / |Xp[d]|^2 (pilot subcarriers only)
@@ -29,6 +30,9 @@ hipError_t launch_estimate(const LaunchArgs& la, float2* H);
 hipError_t launch_g(const LaunchArgs& la, const float2* H, float* g);
 // Both combiners: with one user ZF is MRC normalised by the channel energy.
 hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits);
+// The whole path without an estimate for the caller; scratch: A U 8 bytes per
+// slot.
+hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits);
 hipError_t launch_fft(const LaunchArgs& la, float2* Y);
 // rx_process_frame with the estimate in a fixed buffer, slots in chunks that
 // fit it (rx_api.cpp); returns an rx_status.
