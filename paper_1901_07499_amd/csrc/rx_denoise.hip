@@ -814,6 +814,11 @@ __device__ __forceinline__ float2 normal_pair(uint64_t wa, uint64_t wb) {
   return make_float2(rr * cs, rr * sn);
 }
 
+// One workgroup per row (up to kGenGrid resident ones).  Bound: the tap sums,
+// one twiddle read from LDS per tap and subcarrier.  The twiddle index is the
+// product of signed frequency and delay modulo N, a power of two, so a mask of
+// a 32-bit product (|f| < 1024, delay < 2048); as a 64-bit remainder it took
+// most of the kernel.  A Philox block gives two normals: one thread draws both.
 __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed, int64_t first_row, int64_t rows,
                                                         float2* __restrict__ Htrue, float2* __restrict__ Hls) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -822,6 +827,7 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
   float2* pil = ht + g.U;                        // [U / ps + 1]
   __shared__ float2 taps[64];
   __shared__ int delays[64];
+  __shared__ float power[64];
   const int tid = threadIdx.x, N = g.N, U = g.U, ps = g.ps;
   for (int m = tid; m < N; m += kBlock) {
     float sn, cs;
@@ -838,16 +844,18 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
     const int span = g.tau_min + int_draw(w[1], g.tau_max - g.tau_min + 1);
     const float snr_db = g.snr_min + (g.snr_max - g.snr_min) * unit_u(w[2]);
     __syncthreads();  // previous row's readers of taps / ht / pil are done
+    if (tid < L) power[tid] = exp10f(-g.decay_db * (float)tid / 10.0f);
+    __syncthreads();
     if (tid < L) {
       const int l = tid;
       float psum = 0.f;
-      for (int i = 0; i < L; i++) psum += exp10f(-g.decay_db * (float)i / 10.0f);
+      for (int i = 0; i < L; i++) psum += power[i];
       const int dl = L > 1 ? (l * span + (L - 1) / 2) / (L - 1) : 0;
       delays[l] = dl < g.CP ? dl : g.CP;
       uint64_t b[4];
       philox((uint64_t)(1 + l / 2), row, seed, b);
       const float2 z = (l % 2 == 0) ? normal_pair(b[0], b[1]) : normal_pair(b[2], b[3]);
-      const float a = sqrtf(exp10f(-g.decay_db * (float)l / 10.0f) / psum * 0.5f);
+      const float a = sqrtf(power[l] / psum * 0.5f);
       taps[l] = make_float2(a * z.x, a * z.y);
     }
     __syncthreads();
@@ -855,7 +863,7 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
       const int f = d < U / 2 ? d - U / 2 : d - U / 2 + 1;
       float2 acc = make_float2(0.f, 0.f);
       for (int l = 0; l < L; l++) {
-        const int m = (int)((((int64_t)f * delays[l]) % N + N) % N);
+        const int m = (f * delays[l]) & (N - 1);
         const float2 e = tw[m], h = taps[l];
         acc.x += h.x * e.x - h.y * e.y;
         acc.y += h.x * e.y + h.y * e.x;
@@ -866,12 +874,18 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
     __syncthreads();
     if (Hls) {
       const float sd = sqrtf(exp10f(-snr_db / 10.0f) * 0.5f);
-      for (int j = tid; j < n_pil; j += kBlock) {
+      for (int i = tid; 2 * i < n_pil; i += kBlock) {
         uint64_t b[4];
-        philox((uint64_t)(noise_block + j / 2), row, seed, b);
-        const float2 z = (j % 2 == 0) ? normal_pair(b[0], b[1]) : normal_pair(b[2], b[3]);
-        const float2 h = ht[j * ps];
-        pil[j] = make_float2(h.x + sd * z.x, h.y + sd * z.y);
+        philox((uint64_t)(noise_block + i), row, seed, b);
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          const int j = 2 * i + e;
+          if (j < n_pil) {
+            const float2 z = normal_pair(b[2 * e], b[2 * e + 1]);
+            const float2 h = ht[j * ps];
+            pil[j] = make_float2(h.x + sd * z.x, h.y + sd * z.y);
+          }
+        }
       }
       __syncthreads();
       for (int d = tid; d < U; d += kBlock) Hls[rr * U + d] = comb_value(pil, d, U, ps);
@@ -884,6 +898,7 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
 // ------------------------------------------------------------------ launchers
 namespace {
 constexpr int kMaxGrid = 512;
+constexpr int kGenGrid = 1024;  // generator workgroups: 28 KB of LDS at N = 2048, U = 1200: up to 5 per CU
 size_t fwd_lds(int U) { return (size_t)2 * dn::NPOS * dn::RS * 2 + dn::NPOS * 4 + (size_t)U * 8; }
 size_t bwd_lds() { return (size_t)2 * dn::NPOS * dn::RS * 2 + dn::NPOS * 4; }
 }  // namespace
@@ -944,7 +959,8 @@ hipError_t dn_train(const float2* Hin, const float2* Htrue, int64_t rows, int U,
 hipError_t dn_generate(const GenArgs& g, uint64_t seed, int64_t first_row, int64_t rows, float2* Htrue,
                        float2* Hls, hipStream_t st) {
   const size_t lds = (size_t)g.N * 8 + (size_t)g.U * 8 + (size_t)((g.U - 1) / g.ps + 1) * 8;
-  hipLaunchKernelGGL(dn::dn_gen_kernel, dim3(dn_grid(rows)), dim3(dn::kBlock), lds, st, g, seed, first_row, rows,
+  const int grid = (int)(rows < kGenGrid ? rows : kGenGrid);
+  hipLaunchKernelGGL(dn::dn_gen_kernel, dim3(grid), dim3(dn::kBlock), lds, st, g, seed, first_row, rows,
                      Htrue, Hls);
   return hipGetLastError();
 }
