@@ -48,6 +48,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "rx_comb.hpp"
 #include "rx_launch.h"
 
@@ -541,14 +543,22 @@ __global__ __launch_bounds__(kBlock) void dn_backward_kernel(int64_t rows, int U
 }
 
 // ------------------------------------------------------------------ weight gradients
-// Chunks of 64 positions of one row are staged channel-major in LDS:
-// deltas dT[co][0..63] (row stride 72) and inputs xT[ci][0..79] holding
-// positions q0-8 .. q0+71 (row stride 88; both strides make the 16-byte
-// fragment reads conflict-free).  Per 32-position K step, lane (r, q) of the
-// A operand reads delta row co = r at positions 8q..8q+7; the B operand for
-// tap k needs input row ci = r at positions 8q+k-3 .. 8q+k+4, cut out of
-// three aligned 16-byte reads with a compile-time shift.
-constexpr int CHUNK = 64, DT_RS = 72, XT_RS = 88;
+// Chunks of 128 positions of one row are staged channel-major in LDS: deltas
+// dT[co][0..127] (row stride 136) and inputs xT[ci][0..143] holding positions
+// q0-8 .. q0+135 (row stride 152; both strides make the 16-byte fragment reads
+// conflict-free), the next chunk's loads in flight during this one's products.
+// Per 32-position K step, lane (r, q) of the A operand reads delta row co = r
+// at positions 8q..8q+7; the B operand for tap k needs input row ci = r at
+// positions 8q+k-3 .. 8q+k+4, cut out of three aligned 16-byte reads with a
+// compile-time shift.  The bias gradient is one more product, with ones.
+// Wavefront w takes the K steps of half w >> 1 of a chunk and half w & 1 of
+// the input channels (of the output channels where there are two input
+// channels), all taps and output channels, so an operand read serves as many
+// products as it can; the two halves of the positions meet in LDS at the end.
+// Bound: reading the deltas and activations once, 0.32 GB for 1024 rows of 1200
+// (60 us at the rate of a large copy); 134 us, 288 with 64-position chunks
+// loaded between their barriers and the bias summed by one thread per channel.
+constexpr int CHUNK = 128, DT_RS = 136, XT_RS = 152;
 
 template <int O>
 __device__ __forceinline__ bf16x8 shifted(const uint4& cm, const uint4& c0, const uint4& cp) {
@@ -566,160 +576,203 @@ __device__ __forceinline__ bf16x8 shifted(const uint4& cm, const uint4& c0, cons
   return as_bf16x8(make_uint4(o[0], o[1], o[2], o[3]));
 }
 
-template <int K>
-__device__ __forceinline__ void tap_mfma(const uint4& cm, const uint4& c0, const uint4& cp, const bf16x8& a,
-                                         f32x4& acc) {
-  acc = mfma(a, shifted<K - 3>(cm, c0, cp), acc);
-}
-
-// Stage channels [0, nch) of G (channel-major, pitch UP) for positions
-// q0+off .. q0+off+8*n8-1 into T (row stride rs), zero outside [0, U).
-__device__ __forceinline__ void stage(bfbits* __restrict__ T, int rs, const bfbits* __restrict__ G, int64_t UP,
-                                      int nch, int q0, int off, int n8, int U) {
-  for (int i = threadIdx.x; i < nch * n8; i += kBlock) {
-    const int ch = i / n8, c = i % n8;
-    const int p = q0 + off + 8 * c;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (p >= 0 && p < U) {
-      v = *reinterpret_cast<const uint4*>(G + ch * UP + p);
-      if (p + 8 > U) {  // zero the positions past U
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+// This thread's 16-byte pieces of NCH channels of G (channel-major, pitch UP),
+// positions p0 .. p0 + 8 N8 - 1, zero outside [0, U): loaded, then stored into T
+// (row stride rs).
+template <int NCH, int N8>
+struct Stage {
+  static constexpr int kUnits = NCH * N8, kPer = (kUnits + kBlock - 1) / kBlock;
+  uint4 v[kPer];
+  __device__ __forceinline__ void load(const bfbits* __restrict__ G, int64_t UP, int p0, int U) {
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+      const int i = threadIdx.x + k * kBlock;
+      const int ch = i / N8, p = p0 + 8 * (i % N8);
+      v[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (i < kUnits && p >= 0 && p < U) v[k] = *reinterpret_cast<const uint4*>(G + ch * UP + p);
+    }
+  }
+  __device__ __forceinline__ void store(bfbits* __restrict__ T, int rs, int p0, int U) {
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+      const int i = threadIdx.x + k * kBlock;
+      const int ch = i / N8, c = i % N8, p = p0 + 8 * c;
+      if (p < U && p + 8 > U) {  // zero the positions past U
+        uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
 #pragma unroll
         for (int j = 0; j < 8; j++)
           if (p + j >= U) w[j >> 1] &= (j & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-        v = make_uint4(w[0], w[1], w[2], w[3]);
+        v[k] = make_uint4(w[0], w[1], w[2], w[3]);
       }
+      if (i < kUnits) *reinterpret_cast<uint4*>(T + ch * rs + 8 * c) = v[k];
     }
-    *reinterpret_cast<uint4*>(T + ch * rs + 8 * c) = v;
   }
-}
+};
 
-// Accumulate the weight gradient of one layer over rows [r0, r1).
-// CIN, COUT in {2, 32}.  Wave roles: for 32 x 32 layers wave w owns output
-// channel half w&1 and input channel half w>>1, all 7 taps; for layers with
-// 2 channels on one side, wave w owns half w&1 of the 32-channel side and
-// the taps of parity w>>1.
+// Weight gradient of one layer over rows [r0, r1).  CIN, COUT in {2, 32}.
 template <int CIN, int COUT>
-__device__ void wgrad_layer(const bfbits* __restrict__ D, const bfbits* __restrict__ X, int64_t UP, int U,
+__device__ __forceinline__ void wgrad_layer(const bfbits* __restrict__ D, const bfbits* __restrict__ X, int64_t UP, int U,
                             int64_t r0, int64_t r1, bfbits* dT, bfbits* xT, float* __restrict__ out_w,
                             float* __restrict__ out_b) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
-  constexpr bool FULL = CIN == 32 && COUT == 32;
-  const int ch_half = wave & 1;       // output-channel half (FULL, or CIN == 2) / input half (COUT == 2)
-  const int other_half = wave >> 1;   // input-channel half (FULL) / tap parity (otherwise)
-  f32x4 acc[7];
+  constexpr int NA = CIN == 32 && COUT == 32 ? 2 : 1;  // output-channel halves of this wavefront
+  const int half = wave & 1, ph = wave >> 1;
+  const int co_base = COUT == 32 && NA == 1 ? 16 * half : 0, ci_base = CIN == 32 ? 16 * half : 0;
+  const bool bias = CIN == 2 || half == 0;
+  f32x4 acc[NA][7], accb[NA];
 #pragma unroll
-  for (int k = 0; k < 7; k++) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float bacc = 0.f;
-  // rows of the A (delta) and B (input) operands this lane reads
-  const int co_row = COUT == 32 ? 16 * ch_half + r : r;                      // valid if < COUT
-  const int ci_row = CIN == 32 ? 16 * (FULL ? other_half : ch_half) + r : r;  // valid if < CIN
-  const bool a_ok = co_row < COUT, b_ok = ci_row < CIN;
+  for (int h = 0; h < NA; h++) {
+    accb[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 7; k++) acc[h][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const bool a_ok = COUT == 32 || r < 2, b_ok = CIN == 32 || r < 2;
+  const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 
-  for (int64_t row = r0; row < r1; row++) {
-    for (int q0 = 0; q0 < U; q0 += CHUNK) {
-      __syncthreads();
-      stage(dT, DT_RS, D + row * COUT * UP, UP, COUT, q0, 0, CHUNK / 8, U);
-      stage(xT, XT_RS, X + row * CIN * UP, UP, CIN, q0, -8, CHUNK / 8 + 2, U);
-      __syncthreads();
-      if (tid < COUT) {
-        float sacc = 0.f;
-        for (int j = 0; j < CHUNK; j++) sacc += bf16_float(dT[tid * DT_RS + j]);
-        bacc += sacc;
-      }
+  Stage<COUT, CHUNK / 8> sd;
+  Stage<CIN, CHUNK / 8 + 2> sx;
+  int64_t row = r0;
+  int q0 = 0;
+  auto load = [&]() {
+    sd.load(D + row * COUT * UP, UP, q0, U);
+    sx.load(X + row * CIN * UP, UP, q0 - 8, U);
+  };
+  if (r0 < r1) load();
+  const int chunks = (U + CHUNK - 1) / CHUNK;
+  const int64_t n = (r1 - r0) * chunks;
+  for (int64_t it = 0; it < n; it++) {
+    __syncthreads();  // the previous chunk's readers are done
+    sd.store(dT, DT_RS, q0, U);
+    sx.store(xT, XT_RS, q0 - 8, U);
+    __syncthreads();
+    q0 += CHUNK;
+    if (q0 >= U) {
+      q0 = 0;
+      row++;
+    }
+    if (it + 1 < n) load();
 #pragma unroll
-      for (int ks = 0; ks < CHUNK / 32; ks++) {
-        const int pos = 32 * ks + 8 * q;
-        const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-        const uint4 av = a_ok ? *reinterpret_cast<const uint4*>(dT + co_row * DT_RS + pos) : z;
-        const bf16x8 a = as_bf16x8(av);
-        const bfbits* xr = xT + ci_row * XT_RS + 8 + pos;
-        const uint4 cm = b_ok ? *reinterpret_cast<const uint4*>(xr - 8) : z;
-        const uint4 c0 = b_ok ? *reinterpret_cast<const uint4*>(xr) : z;
-        const uint4 cp = b_ok ? *reinterpret_cast<const uint4*>(xr + 8) : z;
-        if constexpr (FULL) {
-          tap_mfma<0>(cm, c0, cp, a, acc[0]);
-          tap_mfma<1>(cm, c0, cp, a, acc[1]);
-          tap_mfma<2>(cm, c0, cp, a, acc[2]);
-          tap_mfma<3>(cm, c0, cp, a, acc[3]);
-          tap_mfma<4>(cm, c0, cp, a, acc[4]);
-          tap_mfma<5>(cm, c0, cp, a, acc[5]);
-          tap_mfma<6>(cm, c0, cp, a, acc[6]);
-        } else if (other_half == 0) {
-          tap_mfma<0>(cm, c0, cp, a, acc[0]);
-          tap_mfma<2>(cm, c0, cp, a, acc[2]);
-          tap_mfma<4>(cm, c0, cp, a, acc[4]);
-          tap_mfma<6>(cm, c0, cp, a, acc[6]);
-        } else {
-          tap_mfma<1>(cm, c0, cp, a, acc[1]);
-          tap_mfma<3>(cm, c0, cp, a, acc[3]);
-          tap_mfma<5>(cm, c0, cp, a, acc[5]);
+    for (int ks = 0; ks < CHUNK / 64; ks++) {
+      const int pos = 64 * ph + 32 * ks + 8 * q;
+      bf16x8 a[NA];
+#pragma unroll
+      for (int h = 0; h < NA; h++)
+        a[h] = as_bf16x8(a_ok ? *reinterpret_cast<const uint4*>(dT + (co_base + 16 * h + r) * DT_RS + pos) : zero);
+      const bfbits* xr = xT + (ci_base + r) * XT_RS + 8 + pos;
+      const uint4 cm = b_ok ? *reinterpret_cast<const uint4*>(xr - 8) : zero;
+      const uint4 c0 = b_ok ? *reinterpret_cast<const uint4*>(xr) : zero;
+      const uint4 cp = b_ok ? *reinterpret_cast<const uint4*>(xr + 8) : zero;
+      auto taps = [&](auto tap) {
+        const bf16x8 b = shifted<decltype(tap)::value - 3>(cm, c0, cp);
+#pragma unroll
+        for (int h = 0; h < NA; h++) acc[h][decltype(tap)::value] = mfma(a[h], b, acc[h][decltype(tap)::value]);
+      };
+      taps(std::integral_constant<int, 0>{});
+      taps(std::integral_constant<int, 1>{});
+      taps(std::integral_constant<int, 2>{});
+      taps(std::integral_constant<int, 3>{});
+      taps(std::integral_constant<int, 4>{});
+      taps(std::integral_constant<int, 5>{});
+      taps(std::integral_constant<int, 6>{});
+      if (bias)
+#pragma unroll
+        for (int h = 0; h < NA; h++) accb[h] = mfma(a[h], ones, accb[h]);
+    }
+  }
+  // the two position halves: wavefronts 2 and 3 hand their sums over in LDS,
+  // one output-channel half at a time
+  f32x4* sh = reinterpret_cast<f32x4*>(dT) + (int64_t)half * 8 * 64 + lane;
+#pragma unroll
+  for (int h = 0; h < NA; h++) {
+    __syncthreads();
+    if (ph == 1) {
+#pragma unroll
+      for (int k = 0; k < 7; k++) sh[k * 64] = acc[h][k];
+      sh[7 * 64] = accb[h];
+    }
+    __syncthreads();
+    if (ph == 0) {
+      // C: lane (r, q), register i -> output channel row 4q+i of the A half, input column r of the B half
+#pragma unroll
+      for (int k = 0; k < 7; k++) {
+        const f32x4 o = sh[k * 64];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const int co = co_base + 16 * h + 4 * q + i, ci = ci_base + r;
+          if (co < COUT && ci < CIN) out_w[(co * CIN + ci) * 7 + k] = acc[h][k][i] + o[i];
         }
       }
+      const f32x4 o = sh[7 * 64];
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int co = co_base + 16 * h + 4 * q + i;
+        if (bias && r == 0 && co < COUT) out_b[co] = accb[h][i] + o[i];
+      }
     }
   }
-  // C: lane (r, q), register i -> output channel row 4q+i of the A half, input column r of the B half
-#pragma unroll
-  for (int k = 0; k < 7; k++) {
-    const bool mine = FULL || ((k & 1) == other_half);
-    if (!mine) continue;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int co = (COUT == 32 ? 16 * ch_half : 0) + 4 * q + i;
-      const int ci = (CIN == 32 ? 16 * (FULL ? other_half : ch_half) : 0) + r;
-      if (co < COUT && ci < CIN) out_w[(co * CIN + ci) * 7 + k] = acc[k][i];
-    }
-  }
-  if (tid < COUT) out_b[tid] = bacc;
 }
 
-__global__ __launch_bounds__(kBlock) void dn_wgrad_kernel(int64_t rows, int U, DnTrainIo io) {
-  __shared__ __align__(16) bfbits dT[32 * DT_RS];
-  __shared__ __align__(16) bfbits xT[32 * XT_RS];
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void dn_wgrad_kernel(int64_t rows, int U, DnTrainIo io) {
+  __shared__ __align__(16) bfbits smem[32 * (DT_RS + XT_RS)];
+  bfbits *dT = smem, *xT = smem + 32 * DT_RS;
+  static_assert(2 * 8 * 64 * 16 <= 32 * (DT_RS + XT_RS) * 2, "the hand-over fits");
   const int64_t G = gridDim.x;
   const int64_t r0 = rows * blockIdx.x / G, r1 = rows * (blockIdx.x + 1) / G;
   float* part = io.part + (int64_t)blockIdx.x * kParams;
   const int64_t UP = io.UP;
-  // one layer per workgroup (grid y): each parameter of partial vector
-  // blockIdx.x is written by exactly one workgroup
+  // one layer per workgroup (grid y, the 32 x 32 ones first): each parameter of
+  // partial vector blockIdx.x is written by exactly one workgroup
   switch (blockIdx.y) {
-    case 0: wgrad_layer<2, 32>(io.D1, io.X0, UP, U, r0, r1, dT, xT, part + kPW1, part + kPB1); break;
-    case 1: wgrad_layer<32, 32>(io.D2, io.X1, UP, U, r0, r1, dT, xT, part + kPW2, part + kPB2); break;
-    case 2: wgrad_layer<32, 32>(io.D3, io.X2, UP, U, r0, r1, dT, xT, part + kPW3, part + kPB3); break;
+    case 0: wgrad_layer<32, 32>(io.D2, io.X1, UP, U, r0, r1, dT, xT, part + kPW2, part + kPB2); break;
+    case 1: wgrad_layer<32, 32>(io.D3, io.X2, UP, U, r0, r1, dT, xT, part + kPW3, part + kPB3); break;
+    case 2: wgrad_layer<2, 32>(io.D1, io.X0, UP, U, r0, r1, dT, xT, part + kPW1, part + kPB1); break;
     default: wgrad_layer<32, 2>(io.D4, io.X3, UP, U, r0, r1, dT, xT, part + kPW4, part + kPB4); break;
   }
 }
 
 // ------------------------------------------------------------------ reduce + Adam
 // grad[i] = sum over workgroup partials g of part[g][i]: a block owns 64
-// parameters; its 4 wavefronts sum the partials g = w, w + 4, ... (in order,
-// coalesced over the 64 parameters), then wavefront 0 adds the 4 sums in
+// parameters; its 16 wavefronts sum the partials g = w, w + 16, ... (in order,
+// coalesced over the 64 parameters), then wavefront 0 adds the 16 sums in
 // order, so the result is deterministic.  Optionally the Adam update of theta,
 // m, v (bias corrections c1 = 1/(1-beta1^t), c2 = 1/(1-beta2^t) from the
-// host).  Block 0 also sums the loss partials.
-constexpr int kRedParams = 64;
+// host).  The last wavefront of block 0 also sums the loss partials, lane by
+// lane, then over the lanes.  Bound: reading the partials (61 KB each); with 4
+// wavefronts and one thread summing the loss partials in a row, 512 partials
+// took 44 us.
+constexpr int kRedParams = 64, kRedWaves = 16;
 
-__global__ __launch_bounds__(kBlock) void dn_reduce_kernel(const float* __restrict__ part, int n_part,
-                                                           const float* __restrict__ loss_part, int n_loss,
-                                                           float* __restrict__ grad, float* __restrict__ loss,
-                                                           AdamArgs adam) {
-  __shared__ float sums[4][kRedParams];
+__global__ __launch_bounds__(64 * kRedWaves) void dn_reduce_kernel(const float* __restrict__ part, int n_part,
+                                                                  const float* __restrict__ loss_part, int n_loss,
+                                                                  float* __restrict__ grad, float* __restrict__ loss,
+                                                                  AdamArgs adam) {
+  __shared__ float sums[kRedWaves][kRedParams];
   const int j = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int i = blockIdx.x * kRedParams + j;
   float acc = 0.f;
   if (i < kParams) {
     int b = w;
-    for (; b + 12 < n_part; b += 16) {  // four independent loads in flight
-      const float v0 = part[(int64_t)b * kParams + i], v1 = part[(int64_t)(b + 4) * kParams + i];
-      const float v2 = part[(int64_t)(b + 8) * kParams + i], v3 = part[(int64_t)(b + 12) * kParams + i];
-      acc = (((acc + v0) + v1) + v2) + v3;
+    for (; b + 3 * kRedWaves < n_part; b += 4 * kRedWaves) {  // four independent loads in flight
+      float v[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) v[k] = part[(int64_t)(b + k * kRedWaves) * kParams + i];
+      acc = (((acc + v[0]) + v[1]) + v[2]) + v[3];
     }
-    for (; b < n_part; b += 4) acc += part[(int64_t)b * kParams + i];
+    for (; b < n_part; b += kRedWaves) acc += part[(int64_t)b * kParams + i];
   }
   sums[w][j] = acc;
+  if (blockIdx.x == 0 && w == kRedWaves - 1 && loss) {
+    float s = 0.f;
+    for (int b = j; b < n_loss; b += 64) s += loss_part[b];
+    s = wave_sum(s);
+    if (j == 0) *loss = s;
+  }
   __syncthreads();
   if (w == 0 && i < kParams) {
-    const float g = ((sums[0][j] + sums[1][j]) + sums[2][j]) + sums[3][j];
+    float g = 0.f;
+#pragma unroll
+    for (int k = 0; k < kRedWaves; k++) g += sums[k][j];
     if (grad) grad[i] = g;
     if (adam.theta) {
       const float m = adam.beta1 * adam.m[i] + (1.0f - adam.beta1) * g;
@@ -728,11 +781,6 @@ __global__ __launch_bounds__(kBlock) void dn_reduce_kernel(const float* __restri
       adam.v[i] = v;
       adam.theta[i] -= adam.lr * (m * adam.c1) / (sqrtf(v * adam.c2) + adam.eps);
     }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-    float s = 0.f;
-    for (int b = 0; b < n_loss; b++) s += loss_part[b];
-    *loss = s;
   }
 }
 
@@ -818,7 +866,8 @@ __device__ __forceinline__ float2 normal_pair(uint64_t wa, uint64_t wb) {
 // one twiddle read from LDS per tap and subcarrier.  The twiddle index is the
 // product of signed frequency and delay modulo N, a power of two, so a mask of
 // a 32-bit product (|f| < 1024, delay < 2048); as a 64-bit remainder it took
-// most of the kernel.  A Philox block gives two normals: one thread draws both.
+// most of the kernel.  A Philox block gives two normals: one thread draws
+// both.  1024 rows of 1200 subcarriers, 8 to 24 taps: 125 -> 27 us.
 __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed, int64_t first_row, int64_t rows,
                                                         float2* __restrict__ Htrue, float2* __restrict__ Hls) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -898,6 +947,7 @@ __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed
 // ------------------------------------------------------------------ launchers
 namespace {
 constexpr int kMaxGrid = 512;
+constexpr int kWgradGrid = 256;  // row ranges of the weight gradients: 4 workgroups per CU over the layers
 constexpr int kGenGrid = 1024;  // generator workgroups: 28 KB of LDS at N = 2048, U = 1200: up to 5 per CU
 size_t fwd_lds(int U) { return (size_t)2 * dn::NPOS * dn::RS * 2 + dn::NPOS * 4 + (size_t)U * 8; }
 size_t bwd_lds() { return (size_t)2 * dn::NPOS * dn::RS * 2 + dn::NPOS * 4; }
@@ -949,10 +999,11 @@ hipError_t dn_train(const float2* Hin, const float2* Htrue, int64_t rows, int U,
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(dn::dn_backward_kernel, dim3(G), dim3(dn::kBlock), bwd_lds(), st, rows, U, fr, io);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(dn::dn_wgrad_kernel, dim3(G, 4), dim3(dn::kBlock), 0, st, rows, U, io);
+  const int GW = G < kWgradGrid ? G : kWgradGrid;
+  hipLaunchKernelGGL(dn::dn_wgrad_kernel, dim3(GW, 4), dim3(dn::kBlock), 0, st, rows, U, io);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(dn::dn_reduce_kernel, dim3((kParams + dn::kRedParams - 1) / dn::kRedParams), dim3(dn::kBlock), 0, st,
-                     (const float*)io.part, G, (const float*)io.loss_part, G, grad, loss, adam);
+  hipLaunchKernelGGL(dn::dn_reduce_kernel, dim3((kParams + dn::kRedParams - 1) / dn::kRedParams), dim3(64 * dn::kRedWaves), 0, st,
+                     (const float*)io.part, GW, (const float*)io.loss_part, G, grad, loss, adam);
   return hipGetLastError();
 }
 
