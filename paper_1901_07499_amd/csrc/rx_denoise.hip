@@ -79,7 +79,7 @@ constexpr int BASE_B = 18; // backward: LDS index of position t0
 constexpr int U1 = 17, U2 = 16, U3 = 16, U4P = 16;
 constexpr int PS = 260;  // LDS row pitch (floats) of the folded last layer's per-tap outputs
 static_assert(14 * PS * 4 <= NPOS * RS * 2, "per-tap outputs fit in one activation buffer");
-constexpr int BU3 = 16, BU2 = 16, BU1 = 15;
+constexpr int BU2 = 16, BU1 = 15;  // (the first transposed layer: 16)
 
 __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -118,30 +118,15 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One GEMM unit of a 32-input-channel layer: 16 positions, 32 output channels
-// (acc[h] holds output channels 16 h .. 16 h + 15).  `row0` is the LDS index
-// of the unit's first position minus the tap offset (tap k reads row0 + k + r).
-// SIGN = +1: forward taps; -1: transposed (tap k reads row0 - k + r).
-template <int SIGN>
-__device__ __forceinline__ void unit32(const bfbits* __restrict__ X, int row0, const bf16x8 (&w)[2][7],
-                                       f32x4 (&acc)[2]) {
-  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
-  bf16x8 b[7];
-#pragma unroll
-  for (int k = 0; k < 7; k++)
-    b[k] = as_bf16x8(*reinterpret_cast<const uint4*>(X + (row0 + SIGN * k + r) * RS + 8 * q));
-#pragma unroll
-  for (int k = 0; k < 7; k++) {
-    acc[0] = mfma(w[0][k], b[k], acc[0]);
-    acc[1] = mfma(w[1][k], b[k], acc[1]);
-  }
-}
-
-// The 7 tap operands of a unit (the loads of unit32, apart from its products).
+// The 7 tap operands of a GEMM unit of a 32-input-channel layer: 16 positions,
+// 32 output channels.  `row0` is the LDS index of the unit's first position
+// minus the tap offset: tap k reads row0 + SIGN k + r, SIGN = +1 forward, -1
+// transposed.
+template <int SIGN = 1>
 __device__ __forceinline__ void unit32_load(const bfbits* __restrict__ X, int row0, bf16x8 (&b)[7]) {
   const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
 #pragma unroll
-  for (int k = 0; k < 7; k++) b[k] = as_bf16x8(*reinterpret_cast<const uint4*>(X + (row0 + k + r) * RS + 8 * q));
+  for (int k = 0; k < 7; k++) b[k] = as_bf16x8(*reinterpret_cast<const uint4*>(X + (row0 + SIGN * k + r) * RS + 8 * q));
 }
 
 // Four dwords at dword index i of an LDS buffer of 2-channel positions
@@ -162,13 +147,27 @@ __device__ __forceinline__ void store_unit(bfbits* __restrict__ Y, int idx, cons
   }
 }
 
-// Channel-major global store of a unit: G[(ch)*UP + p].
-__device__ __forceinline__ void store_global(bfbits* __restrict__ G, int64_t UP, int p, const f32x4 (&v)[2]) {
-  const int q = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int h = 0; h < 2; h++)
-#pragma unroll
-    for (int i = 0; i < 4; i++) G[(int64_t)(16 * h + 4 * q + i) * UP + p] = (bfbits)bf16_bits(v[h][i]);
+// Store the tile's own positions [t0, t0 + TO) of a layer in X (LDS index of
+// position p is p - t0 + base; zero past U) channel-major: G[ch * UP + p], UP a
+// multiple of 8.  A transposing LDS read gives each lane of 16 four positions
+// of one channel, two make a 16-byte piece, and the four groups of a wavefront
+// store 64 bytes of each of 16 channels, where the product's own registers
+// hold one position of 8 channels (2 bytes a store; the training forward of
+// 1024 rows took 110 us with those, 95 with these).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_channels(const bfbits* X, int base, int t0, int U, bfbits* __restrict__ G,
+                                               int64_t UP) {
+  const int r = threadIdx.x & 15, n = 2 * ((min(TO, U - t0) + 7) / 8);  // (8 positions, 16 channels) pieces
+  for (int i = threadIdx.x >> 4; i < n; i += kBlock / 16) {
+    // consecutive groups of lanes take consecutive positions
+    const int p8 = 8 * (i >= n / 2 ? i - n / 2 : i), ch = i >= n / 2 ? 16 : 0;
+    const bfbits* src = X + (base + p8 + (r >> 2)) * RS + ch + 4 * (r & 3);
+    typedef __attribute__((address_space(3))) s16x4 lds4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)src);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(src + 4 * RS));
+    const uint2 lo = __builtin_bit_cast(uint2, a), hi = __builtin_bit_cast(uint2, b);
+    *reinterpret_cast<uint4*>(G + (ch + r) * UP + t0 + p8) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+  }
 }
 
 // ReLU mask words of the tile's own positions [t0, t0 + TO) of a layer just
@@ -264,6 +263,28 @@ __device__ __forceinline__ void layer32_paired(const bfbits* __restrict__ X, bfb
   }
 }
 
+// The same, one unit at a time: the training forward, whose registers do not
+// hold a pair's operands (95 us against 109 for 1024 rows).
+template <int NU>
+__device__ __forceinline__ void layer32_single(const bfbits* __restrict__ X, bfbits* __restrict__ Y, int first,
+                                               int p0, int U, const bf16x8 (&w)[2][7],
+                                               const float* __restrict__ bias) {
+  const int wave = threadIdx.x >> 6, r = threadIdx.x & 15;
+  for (int u = wave; u < NU; u += 4) {
+    bf16x8 b[7];
+    unit32_load(X, first + 16 * u - 3, b);
+    f32x4 acc[2];
+    bias_init(acc, bias);
+#pragma unroll
+    for (int k = 0; k < 7; k++) {
+      acc[0] = mfma(w[0][k], b[k], acc[0]);
+      acc[1] = mfma(w[1][k], b[k], acc[1]);
+    }
+    relu_unit(acc, p0 + 16 * u, U);
+    store_unit(Y, first + 16 * u + r, acc);
+  }
+}
+
 // ------------------------------------------------------------------ forward
 // Halo layout of a forward tile starting at output position t0 (LDS index
 // of position p is p - t0 + 12):
@@ -348,49 +369,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
       // layer 1: x0 -> A
       for (int u = wave; u < U1; u += 4) {
         const int idx = 3 + 16 * u + r;  // LDS index of this lane's output position
-        const int p = t0 - 9 + 16 * u + r;
         const bf16x8 bv = read4(X0, idx - 3 + 4 * q);
         f32x4 acc[2];
         bias_init(acc, b1);
         acc[0] = mfma(w1[0], bv, acc[0]);
         acc[1] = mfma(w1[1], bv, acc[1]);
-        const bool in = p >= 0 && p < U;
         relu_unit(acc, t0 - 9 + 16 * u, U);
         store_unit(XA, idx, acc);
-        if (TRAIN && in && p >= t0 && p < t0 + TO) store_global(io.X1 + row * 32 * UP, UP, p, acc);
       }
       __syncthreads();
-      if (TRAIN) store_masks(XA, t0, U, io.M1 + row * UP);
+      if (TRAIN) {
+        store_masks(XA, t0, U, io.M1 + row * UP);
+        store_channels(XA, BASE_F, t0, U, io.X1 + row * 32 * UP, UP);
+      }
       // layer 2: A -> B
-      if constexpr (!TRAIN) layer32_paired<U2>(XA, XB, 6, t0 - 6, U, w2, b2);
-      else for (int u = wave; u < U2; u += 4) {
-        const int idx = 6 + 16 * u + r;
-        const int p = t0 - 6 + 16 * u + r;
-        f32x4 acc[2];
-        bias_init(acc, b2);
-        unit32<1>(XA, 6 + 16 * u - 3, w2, acc);
-        const bool in = p >= 0 && p < U;
-        relu_unit(acc, t0 - 6 + 16 * u, U);
-        store_unit(XB, idx, acc);
-        if (TRAIN && in && p >= t0 && p < t0 + TO) store_global(io.X2 + row * 32 * UP, UP, p, acc);
-      }
+      if constexpr (TRAIN) layer32_single<U2>(XA, XB, 6, t0 - 6, U, w2, b2);
+      else layer32_paired<U2>(XA, XB, 6, t0 - 6, U, w2, b2);
       __syncthreads();
-      if (TRAIN) store_masks(XB, t0, U, io.M2 + row * UP);
+      if (TRAIN) {
+        store_masks(XB, t0, U, io.M2 + row * UP);
+        store_channels(XB, BASE_F, t0, U, io.X2 + row * 32 * UP, UP);
+      }
       // layer 3: B -> A
-      if constexpr (!TRAIN) layer32_paired<U3>(XB, XA, 9, t0 - 3, U, w3, b3);
-      else for (int u = wave; u < U3; u += 4) {
-        const int idx = 9 + 16 * u + r;
-        const int p = t0 - 3 + 16 * u + r;
-        f32x4 acc[2];
-        bias_init(acc, b3);
-        unit32<1>(XB, 9 + 16 * u - 3, w3, acc);
-        const bool in = p >= 0 && p < U;
-        relu_unit(acc, t0 - 3 + 16 * u, U);
-        store_unit(XA, idx, acc);
-        if (TRAIN && in && p >= t0 && p < t0 + TO) store_global(io.X3 + row * 32 * UP, UP, p, acc);
-      }
+      if constexpr (TRAIN) layer32_single<U3>(XB, XA, 9, t0 - 3, U, w3, b3);
+      else layer32_paired<U3>(XB, XA, 9, t0 - 3, U, w3, b3);
       __syncthreads();
-      if (TRAIN) store_masks(XA, t0, U, io.M3 + row * UP);
+      if (TRAIN) {
+        store_masks(XA, t0, U, io.M3 + row * UP);
+        store_channels(XA, BASE_F, t0, U, io.X3 + row * 32 * UP, UP);
+      }
       // layer 4, taps folded into the MFMA rows: P[(co, k)][p] = sum_ci
       // W4[co][ci][k] x3[ci][p] (rows co * 7 + k, 14 of 16 used) for positions
       // t0 - 3 .. t0 + 252, kept in LDS as float [row][position] in buffer B
@@ -460,9 +467,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 //   g1   computed for t0   + [0, 240) (15 units) -> d1 = g1 [x1 > 0]
 // The transposed layer 4 has K = 32 slots (tap 3+4q-j/2, channel j%2) of which
 // taps 0..6 are real: lane quarter q reads d4 at p-4q .. p-4q+3.
-__device__ __forceinline__ void mask_unit(f32x4 (&acc)[2], const uint32_t* __restrict__ Mg, int p, bool in) {
+__device__ __forceinline__ void mask_unit(f32x4 (&acc)[2], uint32_t m) {
   const int q = (threadIdx.x & 63) >> 4;
-  const uint32_t m = in ? Mg[p] : 0u;
 #pragma unroll
   for (int h = 0; h < 2; h++)
 #pragma unroll
@@ -474,7 +480,37 @@ __device__ __forceinline__ void mask_unit(f32x4 (&acc)[2], const uint32_t* __res
     }
 }
 
-__global__ __launch_bounds__(kBlock) void dn_backward_kernel(int64_t rows, int U, const bf16x8* __restrict__ frag,
+// A transposed 32-channel layer of a tile, two units at a time (see
+// layer32_paired; the NU units' last one may be missing): unit u covers rows
+// first + 16 u + r of Y, reading rows first + 16 u + 3 - k of X for tap k.
+template <int NU>
+__device__ __forceinline__ void back_layer32(const bfbits* __restrict__ X, bfbits* __restrict__ Y, int first,
+                                             const bf16x8 (&w)[2][7], const uint32_t (&mk)[4]) {
+  static_assert(NU > 12 && NU <= 16, "four units per wavefront, the last one perhaps missing");
+  const int wave = threadIdx.x >> 6, r = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < 4; j += 2) {
+    const int u0 = wave + 4 * j, u1 = u0 + 4;
+    bf16x8 b0[7], b1[7];
+    unit32_load<-1>(X, first + 16 * u0 + 3, b0);
+    unit32_load<-1>(X, first + 16 * u1 + 3, b1);  // inside the buffer for u = 15 too
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    f32x4 a0[2] = {z, z}, a1[2] = {z, z};
+#pragma unroll
+    for (int k = 0; k < 7; k++) {
+      a0[0] = mfma(w[0][k], b0[k], a0[0]);
+      a1[0] = mfma(w[0][k], b1[k], a1[0]);
+      a0[1] = mfma(w[1][k], b0[k], a0[1]);
+      a1[1] = mfma(w[1][k], b1[k], a1[1]);
+    }
+    mask_unit(a0, mk[j]);
+    store_unit(Y, first + 16 * u0 + r, a0);
+    mask_unit(a1, mk[j + 1]);
+    if (u1 < NU) store_unit(Y, first + 16 * u1 + r, a1);
+  }
+}
+
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void dn_backward_kernel(int64_t rows, int U, const bf16x8* __restrict__ frag,
                                                              DnTrainIo io) {
   extern __shared__ __align__(16) unsigned char smem[];
   bfbits* DA = reinterpret_cast<bfbits*>(smem);
@@ -497,6 +533,18 @@ __global__ __launch_bounds__(kBlock) void dn_backward_kernel(int64_t rows, int U
   for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
     const bfbits* d4r = io.D4 + row * 2 * UP;
     for (int t0 = 0; t0 < U; t0 += TO) {
+      // the tile's ReLU masks, requested here for the three layers: read at
+      // their use they cost a memory latency per unit (1024 rows: 150 us; with
+      // the masks ahead and two units at a time, 95)
+      uint32_t mk[3][4];
+      const uint32_t* const M[3] = {io.M3 + row * UP, io.M2 + row * UP, io.M1 + row * UP};
+#pragma unroll
+      for (int l = 0; l < 3; l++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const int p = t0 - 6 + 3 * l + 16 * (wave + 4 * j) + r;
+          mk[l][j] = p >= 0 && p < U ? M[l][p] : 0u;
+        }
       __syncthreads();
       for (int i = tid; i < NPOS; i += kBlock) {
         const int p = t0 - BASE_B + i;
@@ -504,40 +552,26 @@ __global__ __launch_bounds__(kBlock) void dn_backward_kernel(int64_t rows, int U
       }
       __syncthreads();
       // transposed layer 4: d4 -> d3 (buffer A)
-      for (int u = wave; u < BU3; u += 4) {
-        const int idx = 12 + 16 * u + r;
-        const int p = t0 - 6 + 16 * u + r;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int idx = 12 + 16 * (wave + 4 * j) + r;
         f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         const bf16x8 bv = read4(D4s, idx - 4 * q);
         acc[0] = mfma(g4[0], bv, acc[0]);
         acc[1] = mfma(g4[1], bv, acc[1]);
-        const bool in = p >= 0 && p < U;
-        mask_unit(acc, io.M3 + row * UP, p, in);
+        mask_unit(acc, mk[0][j]);
         store_unit(DA, idx, acc);
-        if (in && p >= t0 && p < t0 + TO) store_global(io.D3 + row * 32 * UP, UP, p, acc);
       }
       __syncthreads();
+      store_channels(DA, BASE_B, t0, U, io.D3 + row * 32 * UP, UP);
       // transposed layer 3: d3 -> d2 (buffer B)
-      for (int u = wave; u < BU2; u += 4) {
-        const int idx = 15 + 16 * u + r;
-        const int p = t0 - 3 + 16 * u + r;
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        unit32<-1>(DA, 15 + 16 * u + 3, g3, acc);
-        const bool in = p >= 0 && p < U;
-        mask_unit(acc, io.M2 + row * UP, p, in);
-        store_unit(DB, idx, acc);
-        if (in && p >= t0 && p < t0 + TO) store_global(io.D2 + row * 32 * UP, UP, p, acc);
-      }
+      back_layer32<BU2>(DA, DB, 15, g3, mk[1]);
       __syncthreads();
-      // transposed layer 2: d2 -> d1 (global only)
-      for (int u = wave; u < BU1; u += 4) {
-        const int p = t0 + 16 * u + r;
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        unit32<-1>(DB, 18 + 16 * u + 3, g2, acc);
-        const bool in = p < U;
-        mask_unit(acc, io.M1 + row * UP, p, in);
-        if (in) store_global(io.D1 + row * 32 * UP, UP, p, acc);
-      }
+      store_channels(DB, BASE_B, t0, U, io.D2 + row * 32 * UP, UP);
+      // transposed layer 2: d2 -> d1 (buffer A: d3's readers are done)
+      back_layer32<BU1>(DB, DA, 18, g2, mk[2]);
+      __syncthreads();
+      store_channels(DA, BASE_B, t0, U, io.D1 + row * 32 * UP, UP);
     }
   }
 }
