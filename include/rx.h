@@ -181,11 +181,12 @@ int rx_debug_fft(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* Y, v
  * h_off[i] complex entries of the H buffer ([A][U]), its x-hat at x_off[i]
  * complex entries ([T-1][U]) and its bits at b_off[i] bytes ([T-1][U*b/8]).
  * The path per frame is the one of rx_process_frame (paper Sec. II-B and
- * II-C); the batch runs it for every frame in one graph launch.  Frames with
- * equal FFT length share one persistent estimate kernel and one persistent
- * demod kernel that take tiles from device work queues (frames with more
- * antennas first, ties in batch order); different FFT lengths run on
- * independent graph branches.
+ * II-C); the batch runs it for every frame in one graph launch.  At the
+ * default configuration one estimate and one demod kernel (a second pair where
+ * some spectra are much wider) serve every FFT length, the frames with the most
+ * samples first.  Once a length has another configuration, each length has its
+ * own persistent kernels that take tiles from device work queues (frames with
+ * more antennas first, ties in batch order) on independent graph branches.
  * ------------------------------------------------------------------------- */
 typedef struct rx_batch_s* rx_batch_t;
 
@@ -220,7 +221,9 @@ int rx_batch_process(rx_batch_t batch, const int16_t* iq, float* H, float* xhat,
  * class by class from the longest, within the whole batch graph with the
  * other classes as chosen so far: every shape with the class's schedules,
  * then every pair of schedules with the best shape, a choice replaced only
- * by one more than 1 % faster.  The whole batch runs 16 times first, untimed.
+ * by one more than 1 % faster; at the end the default configuration, with its
+ * kernels over all lengths, stays unless the chosen ones are more than 1 %
+ * faster.  The whole batch runs 16 times first, untimed.
  * Synchronous; overwrites the outputs. */
 int rx_batch_autotune(rx_batch_t batch, const int16_t* iq, float* H, float* xhat, uint8_t* bits,
                       void* workspace, int32_t reps, void* hip_stream);

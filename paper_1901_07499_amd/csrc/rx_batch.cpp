@@ -2,16 +2,20 @@
 //
 // A batch is an ordered list of frames (one slot each) whose antenna count,
 // FFT length, CP, used subcarriers, QAM order and pilot may all differ.
-// Frames with the same FFT length form a class; each class runs a persistent
-// estimate kernel followed by a persistent demod kernel that pull (frame,
-// item) tiles from device work queues in frame order.  One graph holds a
-// reset node (clears the queues, stamps the start time) and one two-node
-// branch per class, the branches independent of each other, so one graph
-// launch processes the whole batch.  The autotuner times the launch
-// configurations of every class (workgroup shapes and the FFT's radix
-// schedule, chosen separately for the estimate and demod kernels) on the
-// caller's data, first each class alone and then within the whole graph, and
-// keeps the fastest.
+// Two merged kernel pairs serve the batch: frames whose spectrum fits the
+// 5-register window share an estimate and a demod kernel over all
+// FFT lengths, wider ones another pair; a workgroup is a tile, longest first.
+// One graph holds a reset node (clears queues and counters, stamps the start), the estimate nodes
+// beside it and the demod nodes after both, so one graph launch processes the
+// whole batch.
+// Frames with the same FFT length also form a class with its own kernels and
+// launch configuration (workgroup shapes and the FFT's radix schedule, chosen
+// separately for the estimate and demod kernels).  Once a class's
+// configuration differs from the default, the graph is one two-node branch per
+// class instead, persistent kernels that pull tiles from device work queues.
+// The autotuner times the configurations of every class on the caller's data,
+// first each class alone and then within the whole graph, and keeps the
+// fastest, or the merged kernels if they are.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,6 +47,15 @@ struct BatchClass {
   int dem_grid = 0, est_grid = 0;
 };
 
+// Frames served by one pair of merged kernels.
+struct BatchGroup {
+  rx::BatchMerged k;
+  int n_est = 0, n_dem = 0;
+  rx::FrameDesc* d_desc = nullptr;
+  rx::BatchTile *d_est = nullptr, *d_dem = nullptr;
+  size_t est_lds = 0, dem_lds = 0;
+};
+
 }  // namespace
 
 struct rx_batch_s {
@@ -51,6 +64,7 @@ struct rx_batch_s {
   std::vector<int64_t> iq_off, h_off, x_off, b_off;  // n + 1 entries each
   std::vector<int64_t> pf_off;                       // pilot-factor offset of each frame
   std::vector<BatchClass> cls;
+  std::vector<BatchGroup> groups;
   int device = -1;
   int n_cu = 0;
   float2* d_pf = nullptr;
@@ -82,12 +96,97 @@ void free_all(rx_batch_s* b) {
     (void)hipFree(c.d_dem_map);
     (void)hipFree(c.d_tw);
   }
+  for (auto& g : b->groups) {
+    (void)hipFree(g.d_desc);
+    (void)hipFree(g.d_est);
+    (void)hipFree(g.d_dem);
+  }
   (void)hipFree(b->d_pf);
   (void)hipFree(b->d_queues);
   (void)hipFree(b->d_done_count);
   (void)hipFree(b->d_done_time);
   (void)hipFree(b->d_start);
   delete b;
+}
+
+rx::FrameDesc frame_desc(const rx_batch_s* b, int i) {
+  const rx_params& p = b->p[i];
+  rx::FrameDesc d{};
+  d.iq_off = b->iq_off[i] / 2;
+  d.h_off = b->h_off[i];
+  d.x_off = b->x_off[i];
+  d.b_off = b->b_off[i];
+  d.pf = b->d_pf + b->pf_off[i];
+  d.A = p.n_ant;
+  d.T = p.n_sym;
+  d.CP = p.cp_len;
+  d.U = p.n_used;
+  d.B = p.bits_per_sym;
+  d.index = i;
+  d.N = p.fft_len;
+  return d;
+}
+
+bool default_config(const BatchClass& c) {
+  return c.demod_waves == 4 && c.est_jobs == 4 && c.dem_sched == 0 && c.est_sched == 0;
+}
+bool merged(const rx_batch_s* b) { return std::all_of(b->cls.begin(), b->cls.end(), default_config); }
+
+template <typename T>
+int upload(T** dst, const std::vector<T>& v) {
+  if (hipMalloc(dst, sizeof(T) * v.size()) != hipSuccess) return RX_E_NOMEM;
+  return hipMemcpy(*dst, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice) == hipSuccess ? RX_OK : RX_E_HIP;
+}
+
+// The merged kernels' frames, tiles and launch geometry.  A tile's time goes by
+// its samples, antennas x FFT length: longest first, ties in batch order.
+int build_groups(rx_batch_s* b) {
+  std::vector<int> order(b->p.size());
+  for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
+  const auto cost = [b](int i) { return (int64_t)b->p[i].n_ant * b->p[i].fft_len; };
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
+  // 8 wavefronts per demod workgroup halve the longest tile, 4 fill the chip
+  // better (12 per compute unit against 8): 8 where the longest tile takes about
+  // as long as a compute unit's share of all tiles and is more than one round of
+  // an 8-wavefront workgroup's transforms.  Mixed frames of up to 128 antennas x
+  // 2048 points, us with 8 and with 4: 16 frames 154 and 192, 64 frames 158 and
+  // 201, 100 frames 174 and 210 (share 0.9 of the longest tile), 160 frames 236
+  // and 219 (1.5), 256 frames 392 and 292.
+  int64_t total = 0, longest = 0;
+  for (int i : order) {
+    total += cost(i) * (b->p[i].n_sym - 1);
+    longest = std::max(longest, cost(i));
+  }
+  const int waves = longest > 8 * 1024 && 5 * total <= 6 * longest * b->n_cu ? 8 : 4;
+  for (bool wide : {false, true}) {
+    std::vector<rx::FrameDesc> desc;
+    std::vector<rx::BatchTile> est, dem;
+    BatchGroup g;
+    g.k = rx::batch_merged(wide, waves);
+    for (int i : order) {
+      const rx_params& p = b->p[i];
+      if ((rx::batch_window(p.fft_len, p.n_used) > 5) != wide) continue;
+      const int local = (int)desc.size(), l = __builtin_ctz(p.fft_len) - 6;
+      desc.push_back(frame_desc(b, i));
+      for (int a = 0; a < p.n_ant; a += g.k.est_ants[l]) est.push_back({local, a});
+      for (int t = 1; t < p.n_sym; t++) dem.push_back({local, t});
+      g.est_lds = std::max(g.est_lds, g.k.est_lds[l]);
+      g.dem_lds = std::max({g.dem_lds, g.k.lds_fft[l], g.k.lds_per_u[l] * (size_t)p.n_used});
+    }
+    if (desc.empty()) continue;
+    g.n_est = (int)est.size();
+    g.n_dem = (int)dem.size();
+    b->groups.push_back(g);  // owned from here on
+    BatchGroup& o = b->groups.back();
+    int st = upload(&o.d_desc, desc);
+    if (st == RX_OK) st = upload(&o.d_est, est);
+    if (st == RX_OK) st = upload(&o.d_dem, dem);
+    if (st != RX_OK) return st;
+    if (o.dem_lds > 65536 && hipFuncSetAttribute(o.k.dem, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)o.dem_lds) != hipSuccess)
+      return RX_E_HIP;
+  }
+  return RX_OK;
 }
 
 // (Re)build the descriptors, tile maps and launch geometry of class c for
@@ -103,18 +202,7 @@ int configure_class(rx_batch_s* b, BatchClass& c) {
   std::stable_sort(order.begin(), order.end(), [b](int x, int y) { return b->p[x].n_ant > b->p[y].n_ant; });
   for (int i : order) {
     const rx_params& p = b->p[i];
-    rx::FrameDesc d;
-    d.iq_off = b->iq_off[i] / 2;
-    d.h_off = b->h_off[i];
-    d.x_off = b->x_off[i];
-    d.b_off = b->b_off[i];
-    d.pf = b->d_pf + b->pf_off[i];
-    d.A = p.n_ant;
-    d.T = p.n_sym;
-    d.CP = p.cp_len;
-    d.U = p.n_used;
-    d.B = p.bits_per_sym;
-    d.index = i;
+    rx::FrameDesc d = frame_desc(b, i);
     d.est_tile0 = (int)est_map.size();
     d.dem_tile0 = (int)dem_map.size();
     const int local = (int)desc.size();
@@ -225,7 +313,32 @@ int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
   kp.extra = nullptr;
   hipGraphNode_t reset;
   if (hipGraphAddKernelNode(&reset, b->graph, nullptr, 0, &kp) != hipSuccess) return RX_E_HIP;
-  for (size_t ci = 0; ci < b->cls.size(); ci++) {
+  if (merged(b)) {
+    rx::BatchTwiddles tws{};
+    for (const auto& c : b->cls) tws.tw[__builtin_ctz(c.N) - 6] = c.d_tw;
+    for (size_t gi = 0; gi < b->groups.size(); gi++) {
+      BatchGroup& g = b->groups[gi];
+      rx::BatchIo gio = io;
+      void* ea[] = {&g.d_desc, &g.d_est, &gio, &tws};
+      void* da[] = {&g.d_desc, &g.d_dem, &gio, &tws, &b->d_done_count, &b->d_done_time};
+      hipKernelNodeParams ep{}, dp{};
+      ep.func = const_cast<void*>(g.k.est);
+      ep.gridDim = dim3(g.n_est);
+      ep.sharedMemBytes = (unsigned)g.est_lds;
+      ep.kernelParams = ea;
+      dp.func = const_cast<void*>(g.k.dem);
+      dp.gridDim = dim3(g.n_dem);
+      dp.sharedMemBytes = (unsigned)g.dem_lds;
+      dp.kernelParams = da;
+      ep.blockDim = dim3(g.k.est_block);
+      dp.blockDim = dim3(g.k.dem_block);
+      hipGraphNode_t en, dn;
+      if (hipGraphAddKernelNode(&en, b->graph, nullptr, 0, &ep) != hipSuccess) return RX_E_HIP;
+      const hipGraphNode_t before[] = {en, reset};
+      if (hipGraphAddKernelNode(&dn, b->graph, before, 2, &dp) != hipSuccess) return RX_E_HIP;
+    }
+  }
+  for (size_t ci = 0; ci < b->cls.size() && !merged(b); ci++) {
     const BatchClass& c = b->cls[ci];
     KernelArgs ea, da;
     est_args(b, c, ci, io, ea);
@@ -376,6 +489,7 @@ int rx_batch_create(const rx_params* frames, int32_t n_frames, rx_batch_t* out) 
     }
     st = configure_class(b, c);
   }
+  if (st == RX_OK) st = build_groups(b);
   if (st != RX_OK) {
     free_all(b);
     return st;
@@ -502,13 +616,15 @@ int rx_batch_autotune(rx_batch_t b, const int16_t* iq, float* H, float* xhat, ui
     int w, j, sd, se;
     bool operator==(const Cfg& o) const { return w == o.w && j == o.j && sd == o.sd && se == o.se; }
   };
-  auto time_graph = [&](BatchClass& c, const Cfg& g, float* ms) {
+  auto set = [&](BatchClass& c, const Cfg& g) {
     c.demod_waves = g.w;
     c.est_jobs = g.j;
     c.dem_sched = g.sd;
     c.est_sched = g.se;
-    int rc = configure_class(b, c);
-    if (rc == RX_OK) rc = build_graph(b, io);
+    return configure_class(b, c);
+  };
+  auto time_whole = [&](float* ms) {
+    int rc = build_graph(b, io);
     float m = 1e30f;
     for (int r = 0; r <= reps && rc == RX_OK; r++) {  // first run is a warm-up
       float t = 0.f;
@@ -521,6 +637,10 @@ int rx_batch_autotune(rx_batch_t b, const int16_t* iq, float* H, float* xhat, ui
     }
     *ms = m;
     return rc;
+  };
+  auto time_graph = [&](BatchClass& c, const Cfg& g, float* ms) {
+    const int rc = set(c, g);
+    return rc == RX_OK ? time_whole(ms) : rc;
   };
   for (size_t oi = 0; oi < order.size() && st == RX_OK && b->cls.size() > 1; oi++) {
     BatchClass& c = b->cls[order[oi]];
@@ -542,11 +662,20 @@ int rx_batch_autotune(rx_batch_t b, const int16_t* iq, float* H, float* xhat, ui
     const Cfg shape = best_cfg;
     for (int sd = 0; sd < n_sched; sd++)
       for (int se = 0; se < n_sched; se++) consider(Cfg{shape.w, shape.j, sd, se});
-    c.demod_waves = best_cfg.w;
-    c.est_jobs = best_cfg.j;
-    c.dem_sched = best_cfg.sd;
-    c.est_sched = best_cfg.se;
-    if (st == RX_OK) st = configure_class(b, c);
+    if (st == RX_OK) st = set(c, best_cfg);
+  }
+  // The merged kernels (every class at the default) stay unless the tuned
+  // classes are more than 1 % faster.
+  if (st == RX_OK && !merged(b)) {
+    std::vector<Cfg> tuned;
+    for (const auto& c : b->cls) tuned.push_back(Cfg{c.demod_waves, c.est_jobs, c.dem_sched, c.est_sched});
+    float t_tuned = 0.f, t_merged = 0.f;
+    st = time_whole(&t_tuned);
+    for (auto& c : b->cls)
+      if (st == RX_OK) st = set(c, Cfg{4, 4, 0, 0});
+    if (st == RX_OK) st = time_whole(&t_merged);
+    for (size_t i = 0; i < tuned.size() && st == RX_OK && t_tuned < 0.99f * t_merged; i++)
+      st = set(b->cls[i], tuned[i]);
   }
   drop_graph(b);  // rebuilt for the chosen configurations by the next rx_batch_process
   (void)hipEventDestroy(e0);

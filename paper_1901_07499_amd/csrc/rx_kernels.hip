@@ -1160,6 +1160,80 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
   }
 }
 
+// All frames of a batch in one kernel, whatever their FFT lengths: workgroup =
+// tile, the longest first, so the hardware hands out long tiles of every
+// length together and the batch ends on short ones, and no length waits for
+// another's kernel.  (As one pair of persistent kernels per length on graph
+// branches, 256 mixed frames took 372 us: the runtime put five branches on
+// three hardware queues, and the 1024-point class ran by itself behind the
+// 2048-point one, 120 us with most of the chip idle.)
+// Last-pass twiddles in the LDS table for the 5-register window and 4
+// wavefronts, which keeps the kernel at 3 wavefronts per SIMD; the others run 2
+// either way.
+template <int N, int QH, int W>
+using BatchTw = FftTwiddles<N, 0, (QH <= 5 && W == 4)>;
+
+template <int N, int QH, int W>
+__device__ __forceinline__ void batch_demod_length(const FrameDesc& d, const BatchIo& io, int t,
+                                                   const float2* __restrict__ tw, float2* lds, float2* twtab) {
+  BatchTw<N, QH, W> twr;
+  tile_setup(twr, twtab, tw);
+  SlotView sv;
+  sv.iq = io.iq + d.iq_off;
+  sv.H = io.H + d.h_off;
+  sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
+  sv.bits = io.bits ? io.bits + d.b_off : nullptr;
+  sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
+  demod_tile<N, QH, W>(sv, t, lds, twr);
+}
+
+template <int QH, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(QH <= 5 && W == 4 ? 3 : 2)))
+void batch_merged_demod_kernel(const FrameDesc* __restrict__ fd, const BatchTile* __restrict__ tiles, BatchIo io,
+                               BatchTwiddles tws, int* done_count, unsigned long long* done_time) {
+  extern __shared__ float2 lds[];
+  __shared__ float2 twtab[BatchTw<2048, QH, W>::kLdsFloat2 + 1];
+  const BatchTile t = tiles[blockIdx.x];
+  const FrameDesc d = fd[t.frame];
+  switch (d.N) {
+    case 64: batch_demod_length<64, QH, W>(d, io, t.at, tws.tw[0], lds, twtab); break;
+    case 128: batch_demod_length<128, QH, W>(d, io, t.at, tws.tw[1], lds, twtab); break;
+    case 256: batch_demod_length<256, QH, W>(d, io, t.at, tws.tw[2], lds, twtab); break;
+    case 512: batch_demod_length<512, QH, W>(d, io, t.at, tws.tw[3], lds, twtab); break;
+    case 1024: batch_demod_length<1024, QH, W>(d, io, t.at, tws.tw[4], lds, twtab); break;
+    default: batch_demod_length<2048, QH, W>(d, io, t.at, tws.tw[5], lds, twtab); break;
+  }
+  __syncthreads();  // outputs written; the frame's last data symbol completes it
+  if (threadIdx.x == 0 && atomicAdd(done_count + d.index, 1) == d.T - 2)
+    done_time[d.index] = __builtin_amdgcn_s_memrealtime();
+}
+
+// Estimate: workgroup = tile, the longest first; it starts beside the reset
+// kernel.
+template <int N, int QH, int W, int J>
+__device__ __forceinline__ void batch_estimate_length(const FrameDesc& d, const BatchIo& io, int a_wg,
+                                                      const float2* __restrict__ tw, float2* lds) {
+  FftTwiddles<N, 0, false> twr;
+  tile_setup<N>(twr, (float2*)nullptr, tw);
+  estimate_tile<N, W, J, QH, false>(io.iq + d.iq_off, d.A, d.CP, d.U, d.pf, io.H + d.h_off, a_wg, lds, twr, 1);
+}
+
+template <int QH, int W, int J>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void batch_merged_estimate_kernel(
+    const FrameDesc* __restrict__ fd, const BatchTile* __restrict__ tiles, BatchIo io, BatchTwiddles tws) {
+  extern __shared__ float2 lds[];
+  const BatchTile t = tiles[blockIdx.x];
+  const FrameDesc d = fd[t.frame];
+  switch (d.N) {
+    case 64: batch_estimate_length<64, QH, W, J>(d, io, t.at, tws.tw[0], lds); break;
+    case 128: batch_estimate_length<128, QH, W, J>(d, io, t.at, tws.tw[1], lds); break;
+    case 256: batch_estimate_length<256, QH, W, J>(d, io, t.at, tws.tw[2], lds); break;
+    case 512: batch_estimate_length<512, QH, W, J>(d, io, t.at, tws.tw[3], lds); break;
+    case 1024: batch_estimate_length<1024, QH, W, J>(d, io, t.at, tws.tw[4], lds); break;
+    default: batch_estimate_length<2048, QH, W, J>(d, io, t.at, tws.tw[5], lds); break;
+  }
+}
+
 // Start of a batch: clear the work queues and completion counters, stamp the
 // start time (100 MHz device clock).
 __global__ void batch_reset_kernel(int* queues, int n_queues, int* done_count, int n_frames,
@@ -1675,6 +1749,40 @@ bool batch_kernels(int N, int max_u, int demod_waves, int est_jobs, int dem_sche
     case 2048: return batch_pick_n<2048>(max_u, demod_waves, est_jobs, dem_sched, est_sched, dem, est);
     default: return false;
   }
+}
+
+int batch_window(int N, int U) { return (U / 2 + 1 + N / 16 - 1) / (N / 16); }
+
+namespace {
+constexpr int kJobsMerged = 2;
+template <int N, int W>
+void merged_length(BatchMerged& m, int i) {
+  constexpr int tpw = transforms_per_group<N, W>();
+  m.lds_fft[i] = fft_lds_bytes<N, W>();
+  m.lds_per_u[i] = (size_t)tpw * (sizeof(float2) + sizeof(float)) + 2;
+  m.est_ants[i] = transforms_per_group<N, kWavesEst>() * kJobsMerged;
+  m.est_lds[i] = fft_lds_bytes<N, kWavesEst>();
+}
+template <int QH, int W>
+BatchMerged merged_of() {
+  BatchMerged m;
+  m.dem = reinterpret_cast<const void*>(batch_merged_demod_kernel<QH, W>);
+  m.est = reinterpret_cast<const void*>(batch_merged_estimate_kernel<QH, kWavesEst, kJobsMerged>);
+  m.dem_block = 64 * W;
+  m.est_block = 64 * kWavesEst;
+  merged_length<64, W>(m, 0);
+  merged_length<128, W>(m, 1);
+  merged_length<256, W>(m, 2);
+  merged_length<512, W>(m, 3);
+  merged_length<1024, W>(m, 4);
+  merged_length<2048, W>(m, 5);
+  return m;
+}
+}  // namespace
+
+BatchMerged batch_merged(bool wide, int waves) {
+  if (waves == 8) return wide ? merged_of<8, 8>() : merged_of<5, 8>();
+  return wide ? merged_of<8, 4>() : merged_of<5, 4>();
 }
 
 const void* batch_reset_func() { return reinterpret_cast<const void*>(batch_reset_kernel); }

@@ -51,6 +51,17 @@ struct FrameDesc {
   int est_tile0;     // first estimate tile of the frame in its class queue
   int dem_tile0;     // first demod tile of the frame in its class queue
   int index;         // position of the frame in the batch
+  int N;
+};
+
+// One tile of a merged batch kernel: data symbol `at` of a frame (demod), or
+// the group of its antennas that starts with `at` (estimate).
+struct BatchTile {
+  int frame, at;
+};
+// exp(-2 pi i k / N) of every FFT length N = 64 << i (null where no frame has it).
+struct BatchTwiddles {
+  const float2* tw[6];
 };
 
 struct BatchIo {
@@ -81,6 +92,19 @@ bool batch_kernels(int N, int max_u, int demod_waves, int est_jobs, int dem_sche
 int fft_schedule_count(int N);
 void fft_schedule_radices(int N, int sched, int radices[3]);
 const void* batch_reset_func();
+// The merged kernels for frames whose spectrum window has batch_window(N, U)
+// <= 5 registers (wide = 0) or more (wide = 1), with `waves` (4 or 8)
+// wavefronts per demod workgroup.  By FFT length N = 64 << i: LDS of the
+// demod's exchange regions (lds_fft) and of its reduction rows per subcarrier
+// (lds_per_u), LDS and antennas of an estimate tile.
+struct BatchMerged {
+  const void *dem = nullptr, *est = nullptr;
+  int dem_block = 0, est_block = 0;
+  size_t lds_fft[6] = {}, lds_per_u[6] = {}, est_lds[6] = {};
+  int est_ants[6] = {};
+};
+int batch_window(int N, int U);
+BatchMerged batch_merged(bool wide, int waves);
 
 // ---- learned refinement of the channel estimate (rx_denoise.hip)
 // Parameter vector: per layer W[co][ci][7] then b[co]; layers 2->32->32->32->2.
