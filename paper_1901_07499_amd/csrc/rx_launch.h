@@ -162,6 +162,7 @@ hipError_t dn_generate(const GenArgs& g, uint64_t seed, int64_t first_row, int64
 constexpr int kMaxPn = 1024;
 struct SyncChips {  // passed by value as a kernel argument
   int L;
+  int sum;  // of the chips
   int8_t c[kMaxPn];
 };
 int sync_groups(int A, int64_t n_search);

@@ -9,16 +9,18 @@
 // integers (|c| < 2^25 per component, M < 2^64), so the peak decision needs no
 // floating point at all.
 //
-// sync_metric_kernel: workgroup = (1024 candidates, group of antennas); per
-// antenna the workgroup stages the samples its candidates need in LDS and
-// each thread correlates 4 consecutive candidates through a sliding register
-// window.  The staged samples sit in four planes by sample index mod 4, so
-// the window's reads (thread t, sample 4t + m) are consecutive across lanes
-// with compile-time offsets instead of a 4-dword stride (4-way LDS bank
-// conflicts).  The per-group partial metrics are summed by sync_reduce_kernel
-// (integer sums: exact in any order, 16 threads per candidate), which also
-// reduces each 64 candidates to the best (M, n); sync_argmax_kernel reduces
-// those in one workgroup.
+// sync_metric_kernel: workgroup = (1024 candidates, group of antennas).  The
+// correlation of 256 candidates n = n0 + 16 row + col is a product of the
+// antenna's samples [row][kappa] = y[n0 + 16 row + kappa] and the chips as a
+// Toeplitz matrix [kappa][col] = p[kappa - col], kappa < L + 15, on the int8
+// matrix cores (v_mfma_i32_16x16x64_i8, exact): a sample's four bytes (upper
+// and lower byte of either component, the lower one less 128 to be signed) are
+// four operands, and c = 256 C_hi + C_lo + 128 sum p.  The byte planes are
+// staged in LDS, where a row of the operand is 16 consecutive bytes at a
+// multiple of 16.  The per-group partial metrics are summed by
+// sync_reduce_kernel (integer sums: exact in any order, 16 threads per
+// candidate), which also reduces each 64 candidates to the best (M, n);
+// sync_argmax_kernel reduces those in one workgroup.
 // "Best" = larger M, then smaller n: a total order, so the result does not
 // depend on the reduction order.
 // sync_extract_kernel: copies the slots that follow the preamble into the
@@ -33,7 +35,7 @@
 namespace rx {
 namespace sync {
 
-typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;       // threads per metric workgroup
 constexpr int kTile = 4 * kThreads;  // candidates per metric workgroup
@@ -42,13 +44,14 @@ constexpr int kTargetGroups = 2048;  // metric workgroups aimed for (8 per CU)
 constexpr int kRedCand = 64;         // candidates per reduce workgroup
 constexpr int kRedWaves = 16;        // wavefronts per reduce workgroup (threads per candidate)
 
-// Dwords per sample plane of the metric kernel's staging buffer: at least a
-// quarter of the staged samples plus the window words the last step
-// requests ahead (thread 255, window index up to L + 7), and 16 more than a
-// multiple of 64 so the four planes' rows fall in different LDS banks.
-__host__ __device__ constexpr int plane_dwords(int L) {
-  return ((kTile + L + 8 + 3) / 4 + 47) / 64 * 64 + 16;
-}
+// K steps of 64 that hold the Toeplitz matrix's L + 15 rows, and the samples
+// a workgroup stages.
+__host__ __device__ constexpr int k_steps(int L) { return (L + 15 + 63) / 64; }
+__host__ __device__ constexpr int staged(int L) { return kTile + 64 * k_steps(L); }
+// LDS: four byte planes, the chip operand of every K step (16 bytes per lane),
+// and the chips with 16 zeros before and enough behind.
+constexpr int kPadChips = 16;
+__host__ __device__ constexpr int metric_lds(int L) { return 4 * staged(L) + k_steps(L) * 1024 + kPadChips + 64 * k_steps(L); }
 
 struct Best {
   uint64_t v;
@@ -79,146 +82,81 @@ __device__ __forceinline__ Best block_best(Best b, Best* sh) {
   return b;
 }
 
-// Partial metric of one antenna group for kTile candidates: thread t owns
-// candidates n0 + 4t .. n0 + 4t + 3 and slides a 4-sample register window
-// along the staged samples, so each LDS read feeds 4 (candidate, chip) pairs.
-
+// Bound: with one antenna per workgroup, staging: 1359 samples for 255 chips,
+// then 20 products per wavefront.  17 344 candidates, 64 antennas, 255 chips:
+// 7.2 us, where 2-way 16-bit dot products, a sliding window of samples in
+// registers, took 21.6 (their instruction rate the bound).
 __global__ __launch_bounds__(kThreads) void sync_metric_kernel(const uint32_t* __restrict__ raw, int A, int ag,
                                                                int64_t n_samples, int64_t stride, SyncChips ch,
                                                                int64_t n_search, uint64_t* __restrict__ part) {
-  extern __shared__ uint32_t ys[];  // 4 planes of plane_dwords(L): sample j at (j % 4) * P + j / 4
-  const int tid = threadIdx.x, L = ch.L;
-  const int P = plane_dwords(L);
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int tid = threadIdx.x, L = ch.L, KK = k_steps(L), span = staged(L);
+  uint8_t* plane = smem;                                    // [4][span]: re lo, re hi, im lo, im hi
+  i32x4* chips = reinterpret_cast<i32x4*>(smem + 4 * span);  // [KK][64]
+  int8_t* pad = reinterpret_cast<int8_t*>(chips + KK * 64);  // chip m at kPadChips + m
   const int64_t n0 = (int64_t)blockIdx.x * kTile;
   const int g = blockIdx.y, a0 = g * ag, a1 = min(A, a0 + ag);
-  const int span = kTile + L + 3;
+  // chips as the second operand: lane (r, q) of step kk holds p[64 kk + 16 q + b - r], b = 0..15
+  for (int i = tid; i < kPadChips + 64 * KK; i += kThreads) {
+    const int m = i - kPadChips;
+    pad[i] = m >= 0 && m < L ? ch.c[m] : (int8_t)0;
+  }
+  __syncthreads();
+  for (int e = tid; e < KK * 64; e += kThreads) {
+    const int8_t* p = pad + kPadChips + 64 * (e >> 6) + 16 * ((e >> 4) & 3) - (e & 15);
+    i32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      w[i] = (int)((uint32_t)(uint8_t)p[4 * i] | (uint32_t)(uint8_t)p[4 * i + 1] << 8 |
+                   (uint32_t)(uint8_t)p[4 * i + 2] << 16 | (uint32_t)(uint8_t)p[4 * i + 3] << 24);
+    chips[e] = w;
+  }
+  const int wave = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
   uint64_t acc[4] = {0, 0, 0, 0};
-  // sample 4t + k of this thread's window: plane k % 4, row t + k / 4
-  auto Y = [&](int k) { return ys[(k & 3) * P + tid + (k >> 2)]; };
   for (int a = a0; a < a1; a++) {
-    __syncthreads();  // the previous antenna's readers are done
+    __syncthreads();  // the chips are there; the previous antenna's readers are done
     const uint32_t* ya = raw + (int64_t)a * stride;
-    for (int j = tid; j < span; j += kThreads) {
+    for (int j = 4 * tid; j < span; j += 4 * kThreads) {
       const int64_t i = n0 + j;
-      ys[(j & 3) * P + (j >> 2)] = i < n_samples ? ya[i] : 0u;
+      uint32_t y[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) y[k] = i + k < n_samples ? ya[i + k] : 0u;
+      // 4 x 4 bytes, transposed
+      const uint32_t t0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);  // bytes 0, 0', 1, 1'
+      const uint32_t t1 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
+      const uint32_t t2 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);  // bytes 2, 2', 3, 3'
+      const uint32_t t3 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+      const uint32_t b[4] = {__builtin_amdgcn_perm(t1, t0, 0x05040100u) ^ 0x80808080u,
+                             __builtin_amdgcn_perm(t1, t0, 0x07060302u),
+                             __builtin_amdgcn_perm(t3, t2, 0x05040100u) ^ 0x80808080u,
+                             __builtin_amdgcn_perm(t3, t2, 0x07060302u)};
+#pragma unroll
+      for (int k = 0; k < 4; k++) *reinterpret_cast<uint32_t*>(plane + k * span + j) = b[k];
     }
     __syncthreads();
-    // Raw sample words in a sliding window: sw0 = samples 4t + m .. + 3,
-    // sw1 = the next four, at the top of the step of chips m .. m + 3.  A
-    // step applies chip pairs (m, m + 1) and (m + 2, m + 3) to the four
-    // candidates with one 2-way 16-bit dot product (exact, into int32) per
-    // candidate and component: re[j] += c_m yr[m + j] + c_(m+1) yr[m + j + 1].
-    // The dot products take the real (imaginary) parts of samples k and k + 1
-    // packed into one word, pr[k - m] (pi[k - m]), built once per k with a
-    // byte permute and kept for the next step (k = m + 4, m + 5 become its
-    // first two).
-    uint32_t sw0[4], sw1[4];
+    i32x4 c[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-      sw0[u] = Y(u);
-      sw1[u] = Y(u + 4);
+    for (int k = 0; k < 4; k++) c[k] = i32x4{0, 0, 0, 0};
+    const uint8_t* rows = plane + 256 * wave + 16 * (r + q);
+    for (int kk = 0; kk < KK; kk++) {
+      const i32x4 p = chips[kk * 64 + lane];
+#pragma unroll
+      for (int k = 0; k < 4; k++)
+        c[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(*reinterpret_cast<const i32x4*>(rows + k * span + 64 * kk), p,
+                                                     c[k], 0, 0, 0);
     }
-    auto pre = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); };
-    auto pim = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };
-    uint32_t pr[6], pi[6];
-    pr[0] = pre(sw0[0], sw0[1]);
-    pi[0] = pim(sw0[0], sw0[1]);
-    pr[1] = pre(sw0[1], sw0[2]);
-    pi[1] = pim(sw0[1], sw0[2]);
-    int re[4] = {0, 0, 0, 0}, im[4] = {0, 0, 0, 0};
-    int m = 0;
-    // Steps of four chips (one little-endian dword of them), software-
-    // pipelined: the next step's chips and samples are requested once this
-    // step has taken its own, so the wait for them falls a whole step after
-    // they were issued.  The samples are requested on every step, also ahead
-    // of a tail of 1..3 chips or of nothing (window indices up to L + 7,
-    // inside the staging planes; those past the staged span are never used).
-    int cn = 0;
-    if (L >= 4) __builtin_memcpy(&cn, ch.c, 4);
-    // One step of chips m .. m + 3 over the window words a (samples m ..),
-    // b (m + 4 ..); requests the next four into n.
-    auto step = [&](int mm, uint32_t (&a)[4], uint32_t (&b)[4], uint32_t (&n)[4]) {
-      const int cw = cn;
-      __builtin_amdgcn_sched_barrier(0);
-      if (mm + 8 <= L) __builtin_memcpy(&cn, ch.c + mm + 4, 4);
+    // lane (r, q), register i: candidate n0 + 256 wave + 16 (4 q + i) + r
 #pragma unroll
-      for (int u = 0; u < 4; u++) n[u] = Y(mm + u + 8);  // window index <= L + 7
-      pr[2] = pre(a[2], a[3]);
-      pi[2] = pim(a[2], a[3]);
-      pr[3] = pre(a[3], b[0]);
-      pi[3] = pim(a[3], b[0]);
-      pr[4] = pre(b[0], b[1]);
-      pi[4] = pim(b[0], b[1]);
-      pr[5] = pre(b[1], b[2]);
-      pi[5] = pim(b[1], b[2]);
-      // chips mm .. mm + 3 as two pairs of int16
-      const s16x2 c01 = {(short)(int8_t)(uint32_t)cw, (short)(int8_t)((uint32_t)cw >> 8)};
-      const s16x2 c23 = {(short)(int8_t)((uint32_t)cw >> 16), (short)(int8_t)((uint32_t)cw >> 24)};
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        re[j] = __builtin_amdgcn_sdot2(__builtin_bit_cast(s16x2, pr[j]), c01, re[j], false);
-        im[j] = __builtin_amdgcn_sdot2(__builtin_bit_cast(s16x2, pi[j]), c01, im[j], false);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        re[j] = __builtin_amdgcn_sdot2(__builtin_bit_cast(s16x2, pr[j + 2]), c23, re[j], false);
-        im[j] = __builtin_amdgcn_sdot2(__builtin_bit_cast(s16x2, pi[j + 2]), c23, im[j], false);
-      }
-      pr[0] = pr[4];
-      pi[0] = pi[4];
-      pr[1] = pr[5];
-      pi[1] = pi[5];
-    };
-    // Three steps per iteration, the three window buffers taking turns (the
-    // roles cycle with period three, so no register copies), then at most
-    // two more steps; the tail reads the window from sw0, sw1.
-    uint32_t sw2[4];
-    for (; m + 12 <= L; m += 12) {
-      step(m, sw0, sw1, sw2);
-      step(m + 4, sw1, sw2, sw0);
-      step(m + 8, sw2, sw0, sw1);
+    for (int i = 0; i < 4; i++) {
+      const int64_t re = 256 * c[1][i] + c[0][i] + 128 * ch.sum, im = 256 * c[3][i] + c[2][i] + 128 * ch.sum;
+      acc[i] += (uint64_t)(re * re) + (uint64_t)(im * im);
     }
-    if (m + 4 <= L) {
-      step(m, sw0, sw1, sw2);
-      m += 4;
-      if (m + 4 <= L) {
-        step(m, sw1, sw2, sw0);
-        m += 4;
-#pragma unroll
-        for (int u = 0; u < 4; u++) {  // window: sw2, sw0
-          sw1[u] = sw0[u];
-          sw0[u] = sw2[u];
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < 4; u++) {  // window: sw1, sw2
-          sw0[u] = sw1[u];
-          sw1[u] = sw2[u];
-        }
-      }
-    }
-    // tail of L mod 4 chips: chip m + e meets sample m + e + j, which is
-    // window word e + j (sw0, then sw1)
-#pragma unroll
-    for (int e = 0; e < 3; e++) {
-      if (m + e < L) {
-        const int c = ch.c[m + e];
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const uint32_t w = (e + j) < 4 ? sw0[(e + j) & 3] : sw1[(e + j) & 3];
-          re[j] += __mul24(c, (int)(int16_t)(w & 0xFFFFu));
-          im[j] += __mul24(c, (int)(int16_t)(w >> 16));
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; j++) acc[j] += (uint64_t)((int64_t)re[j] * re[j]) + (uint64_t)((int64_t)im[j] * im[j]);
   }
   uint64_t* out = part + (int64_t)g * n_search;
 #pragma unroll
-  for (int j = 0; j < 4; j++) {
-    const int64_t n = n0 + 4 * tid + j;
-    if (n < n_search) out[n] = acc[j];
+  for (int i = 0; i < 4; i++) {
+    const int64_t n = n0 + 256 * wave + 16 * (4 * q + i) + r;
+    if (n < n_search) out[n] = acc[i];
   }
 }
 
@@ -317,7 +255,7 @@ hipError_t sync_find(const uint32_t* raw, int A, int64_t n_samples, int64_t stri
   uint64_t* part = static_cast<uint64_t*>(workspace);
   uint64_t* cv = part + (int64_t)G * n_search;
   int64_t* ci = reinterpret_cast<int64_t*>(cv + nb);
-  const size_t lds = sizeof(uint32_t) * 4 * (size_t)sync::plane_dwords(ch.L);
+  const size_t lds = (size_t)sync::metric_lds(ch.L);
   hipLaunchKernelGGL(sync::sync_metric_kernel, dim3((unsigned)tiles, (unsigned)G), dim3(sync::kThreads), lds, st,
                      raw, A, ag, n_samples, stride, ch, n_search, part);
   hipError_t e = hipGetLastError();

@@ -45,6 +45,7 @@ int rx_sync_find(const int16_t* raw, int32_t n_ant, int64_t n_samples, int64_t s
   for (int m = 0; m < pn_len; m++) {
     if (pn[m] < -1 || pn[m] > 1) return RX_E_INVALID_ARG;
     ch.c[m] = pn[m];
+    ch.sum += pn[m];
   }
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return RX_E_HIP;
