@@ -3,7 +3,7 @@
 // A batch is an ordered list of frames (one slot each) whose antenna count,
 // FFT length, CP, used subcarriers, QAM order and pilot may all differ.
 // Two merged kernel pairs serve the batch: frames whose spectrum fits the
-// 5-register window share an estimate and a demod kernel over all
+// narrow register window share an estimate and a demod kernel over all
 // FFT lengths, wider ones another pair; a workgroup is a tile, longest first.
 // One graph holds a reset node (clears queues and counters, stamps the start), the estimate nodes
 // beside it and the demod nodes after both, so one graph launch processes the
@@ -149,9 +149,9 @@ int build_groups(rx_batch_s* b) {
   // better (12 per compute unit against 8): 8 where the longest tile takes about
   // as long as a compute unit's share of all tiles and is more than one round of
   // an 8-wavefront workgroup's transforms.  Mixed frames of up to 128 antennas x
-  // 2048 points, us with 8 and with 4: 16 frames 154 and 192, 64 frames 158 and
-  // 201, 100 frames 174 and 210 (share 0.9 of the longest tile), 160 frames 236
-  // and 219 (1.5), 256 frames 392 and 292.
+  // 2048 points, us with 8 and with 4: 16 frames 141 and 182, 64 frames 147 and
+  // 192, 100 frames 162 and 198 (share 0.9 of the longest tile), 160 frames 225
+  // and 211 (1.5), 256 frames 380 and 272.
   int64_t total = 0, longest = 0;
   for (int i : order) {
     total += cost(i) * (b->p[i].n_sym - 1);
@@ -165,7 +165,7 @@ int build_groups(rx_batch_s* b) {
     g.k = rx::batch_merged(wide, waves);
     for (int i : order) {
       const rx_params& p = b->p[i];
-      if ((rx::batch_window(p.fft_len, p.n_used) > 5) != wide) continue;
+      if (rx::batch_wide(p.fft_len, p.n_used) != wide) continue;
       const int local = (int)desc.size(), l = __builtin_ctz(p.fft_len) - 6;
       desc.push_back(frame_desc(b, i));
       for (int a = 0; a < p.n_ant; a += g.k.est_ants[l]) est.push_back({local, a});

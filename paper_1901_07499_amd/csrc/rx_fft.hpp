@@ -264,27 +264,37 @@ struct LdsTwiddles {
   __device__ __forceinline__ float2 get(int m, int r) const { return tab[((kShared ? 0 : m) * (R - 1) + r - 1) * L + li]; }
 };
 
-// Twiddles of the passes after the first.  With LDS_LAST the last pass of a
-// three-pass schedule reads its twiddles from a per-workgroup LDS table
-// (fewer VGPRs); otherwise they are held in VGPRs (no LDS reads).
+// Twiddles of the passes after the first.  With LDS_LAST the last pass reads
+// its twiddles from a per-workgroup LDS table (fewer VGPRs); otherwise they are
+// held in VGPRs (no LDS reads).
 template <int N, int S = 0, bool LDS_LAST = true>
 struct FftTwiddles {
   static constexpr int kSchedule = S;
   using Rd = Radices<N, S>;
-  static constexpr bool kLdsLast = LDS_LAST && Rd::R3 > 0;
+  static constexpr bool kLdsLast = LDS_LAST, kThree = Rd::R3 > 0;
+  using P2Regs = PassTwiddles<N, Rd::R2, Rd::R1>;
   using P3Regs = PassTwiddles<N, Rd::R3, Rd::R1 * Rd::R2>;
-  using P3Lds = LdsTwiddles<N, Rd::R3, Rd::R1 * Rd::R2>;
-  static constexpr int kLdsFloat2 = kLdsLast ? P3Lds::kCount : 0;  // LDS table size
-  PassTwiddles<N, Rd::R2, Rd::R1> p2;
-  typename std::conditional<kLdsLast, P3Lds, P3Regs>::type p3;
+  using LastLds = typename std::conditional<kThree, LdsTwiddles<N, Rd::R3, Rd::R1 * Rd::R2>,
+                                            LdsTwiddles<N, Rd::R2, Rd::R1>>::type;
+  static constexpr int kLdsFloat2 = kLdsLast ? LastLds::kCount : 0;  // LDS table size
+  typename std::conditional<kLdsLast && !kThree, LastLds, P2Regs>::type p2;
+  typename std::conditional<kLdsLast && kThree, LastLds, P3Regs>::type p3;
   // lds_tab: the filled table (only read when kLdsLast)
   __device__ __forceinline__ void load(const float2* __restrict__ tw, int li, const float2* lds_tab = nullptr) {
-    p2.load(tw, li);
     if constexpr (kLdsLast) {
-      p3.tab = lds_tab;
-      p3.li = li;
-    } else if constexpr (Rd::R3 > 0) {
-      p3.load(tw, li);
+      auto set = [&](auto& p) {
+        p.tab = lds_tab;
+        p.li = li;
+      };
+      if constexpr (kThree) {
+        p2.load(tw, li);
+        set(p3);
+      } else {
+        set(p2);
+      }
+    } else {
+      p2.load(tw, li);
+      if constexpr (kThree) p3.load(tw, li);
     }
   }
 };

@@ -77,6 +77,10 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t n) {
   return (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
 }
 
+// Slot of a (slot, data symbol) item: items number under 2^31 (the calls check
+// it), so a 32-bit division, a quarter of a 64-bit one's instructions.
+__device__ __forceinline__ int64_t slot_of(int64_t item, int Td) { return (uint32_t)item / (uint32_t)Td; }
+
 // ------------------------------------------------------------------ estimate
 // Transforms a workgroup of W wavefronts runs side by side.
 template <int N, int W>
@@ -184,7 +188,7 @@ __device__ __forceinline__ void estimate_tile(const uint32_t* __restrict__ slot_
 template <int N, int S, bool LL>
 __device__ __forceinline__ void tile_setup(FftTwiddles<N, S, LL>& twr, float2* twtab, const float2* __restrict__ tw) {
   if constexpr (FftTwiddles<N, S, LL>::kLdsLast) {
-    FftTwiddles<N, S, LL>::P3Lds::fill(twtab, tw, threadIdx.x, blockDim.x);
+    FftTwiddles<N, S, LL>::LastLds::fill(twtab, tw, threadIdx.x, blockDim.x);
     __syncthreads();
   }
   twr.load(tw, threadIdx.x % FftShape<N>::L, twtab);
@@ -196,7 +200,7 @@ __device__ __forceinline__ void tile_setup(FftTwiddles<N, S, LL>& twr, float2* t
 // every batch kernel), in the LDS table where VGPRs would cost a wavefront
 // (N = 512, and the resident-grid kernel at 3 per SIMD).
 template <int N>
-constexpr bool estimate_twiddles_in_lds() { return N < 1024; }
+constexpr bool estimate_twiddles_in_lds() { return N == 512; }
 
 // The N = 2048 estimate with the 5-register window needs a register budget
 // of 3 wavefronts per SIMD to stay there (the compiler otherwise takes 170
@@ -272,8 +276,9 @@ __global__ __launch_bounds__(64 * W) void estimate_grid_kernel(const uint32_t* _
   using Sh = FftShape<N>;
   static_assert(Sh::WPT == 1, "a transform within one wavefront");
   extern __shared__ float2 lds[];
-  __shared__ float2 twtab[FftTwiddles<N>::kLdsFloat2 > 0 ? FftTwiddles<N>::kLdsFloat2 : 1];
-  FftTwiddles<N> twr;
+  using Tw = FftTwiddles<N, 0, N >= 512>;
+  __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
+  Tw twr;
   tile_setup<N>(twr, twtab, tw);
   const int li = threadIdx.x % Sh::L, ts = threadIdx.x / Sh::L;
   const int f = ts % Sh::F;
@@ -357,7 +362,7 @@ __global__ __launch_bounds__(64 * W) void estimate_grid_kernel(const uint32_t* _
       s++;
     }
     if (j0 + G < jobs) request();
-    estimate_job<N, 0, true, QH, COMB>(v, el, buf, li, twr, jcur < jobs ? H + (s0 * A + a0) * (int64_t)U : nullptr,
+    estimate_job<N, 0, (N >= 512), QH, COMB>(v, el, buf, li, twr, jcur < jobs ? H + (s0 * A + a0) * (int64_t)U : nullptr,
                                        U, ps);
   }
 }
@@ -670,14 +675,20 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
 }
 
 // Where the uniform demod keeps the last pass's twiddles: in VGPRs (no LDS
-// reads in the antenna loop) for N = 1024 and 2048 at the widest spectrum
-// windows, where the kernel keeps its wavefronts per SIMD (3 at the 5-register
-// window, 2 at the 8-register one) and the 5-register kernels were measured
-// faster; elsewhere in the LDS table.  The N = 2048 kernel with the 5-register
+// reads in the antenna loop) where the kernel keeps its wavefronts per SIMD with
+// them -- N = 1024 and 2048 at the widest windows (3 at 5 registers, 2 at 8; the
+// 5-register kernels were measured faster), N <= 256 at up to 5 (3) and at 8 (2)
+// -- and in the LDS table elsewhere.  At N <= 256 with 6 or 7 registers the
+// table is what lets 3 fit (180 to 194 VGPRs without): 16 antennas x 64 points,
+// 52 subcarriers, 14 980 slots, 327 us in the 8-register kernel at 2 per SIMD,
+// 294 in the 7-register one at 3.  The N = 2048 kernel with the 5-register
 // window needs a register budget of 3 wavefronts per SIMD to stay there (168
 // VGPRs; without the bound the compiler takes 169 and drops to 2).
 template <int N, int QH, int W = 4>
-constexpr bool demod_twiddles_in_lds() { return W == 4 && !((N == 1024 || N == 2048) && QH >= 5); }
+constexpr bool demod_twiddles_in_lds() {
+  if (W != 4) return false;
+  return N <= 256 ? QH == 6 || QH == 7 : N == 512 || QH < 5;
+}
 template <int N, int QH, int W>
 constexpr int demod_min_waves() { return W == 8 ? 2 : N == 2048 && QH == 5 ? 3 : 1; }
 
@@ -694,8 +705,8 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
   tile_setup(twr, twtab, tw);
   const int Td = T - 1;
   const int64_t item = xcd_remap(blockIdx.x, S * Td);
-  const int64_t s = item / Td;
-  const int t = 1 + (int)(item % Td);
+  const int64_t s = slot_of(item, Td);
+  const int t = 1 + (int)(item - s * Td);
   SlotView sv;
   sv.iq = iq + s * T * (int64_t)A * (N + CP);
   sv.H = H + s * A * (int64_t)U;
@@ -714,15 +725,18 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
 // + Wa Fa, ...  Each item's Wa Fa partial sums meet in LDS rows (row =
 // transform slot, as in demod_tile); x-hat, decisions and bits follow per item
 // (paper Sec. II-C, MRC paragraph).
-// The N = 1024 items kernel with the 5-register window is held at 3
-// wavefronts per SIMD (168 VGPRs; the compiler would otherwise take 169).
-template <int N, int QH>
-constexpr int demod_items_min_waves() { return N == 1024 && QH == 5 ? 3 : 1; }
+// The items kernels with the 6- and 7-register windows, and the N = 1024 one
+// with 5, are held at 3 wavefronts per SIMD (168 VGPRs); calls too small to fill
+// the chip have no use for the third, and 8 spills less without it.
+template <int N, int QH, bool SPLIT>
+constexpr int demod_items_min_waves() {
+  return !SPLIT && ((N == 1024 && QH == 5) || QH == 6 || QH == 7) ? 3 : 1;
+}
 
 // SPLIT: Fa > 1 is possible (calls too small to fill the chip; its antenna
 // bounds cost the large ones 3 to 6 %).
 template <int N, int QH, int W, bool STAGED, bool SPLIT>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_items_min_waves<N, QH>())))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_items_min_waves<N, QH, SPLIT>())))
 void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
                                                              int T, int CP, int U, int B,
                                                              const float2* __restrict__ tw,
@@ -755,7 +769,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   const int64_t item = item0 + (wave / Wa) * FI + (f >> lfa);
   const int fa = f & (Fa - 1);
   const int64_t ic = item < items ? item : items - 1;
-  const int64_t s = ic / Td;
+  const int64_t s = slot_of(ic, Td);
   const int t = 1 + (int)(ic - s * Td);
   const uint32_t* sym = iq + (s * T + t) * (int64_t)A * (N + CP) + CP;  // antenna 0 of symbol t
   const float2* Hs = H + s * A * (int64_t)U;
@@ -805,7 +819,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
       const int64_t iq_ = item0 + (wave / Wa) * FI + (fq >> lfa);
       sa[q] = fq & (Fa - 1);
       const int64_t icq = iq_ < items ? iq_ : items - 1;
-      const int64_t sq = icq / Td;
+      const int64_t sq = slot_of(icq, Td);
       const int tq = 1 + (int)(icq - sq * Td);
       srec[q] = iq + (sq * T + tq) * (int64_t)A * (N + CP) + CP + (e - fq * N);
     }
@@ -960,7 +974,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
   const int Td = T - 1;
   const int64_t item = blockIdx.x / NB;
   const int b = blockIdx.x % NB;
-  const int64_t s = item / Td;
+  const int64_t s = slot_of(item, Td);
   const int t = 1 + (int)(item - s * Td);
   const int a0 = (int)((int64_t)A * b / NB), na = (int)((int64_t)A * (b + 1) / NB) - a0;
   const int li = threadIdx.x % Sh::L, ts = threadIdx.x / Sh::L;
@@ -975,7 +989,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
   el.init(li, U, pf);
   // last-pass twiddles in the LDS table where the widest window needs the
   // registers
-  using Tw = FftTwiddles<N, 0, QH == 8>;
+  using Tw = FftTwiddles<N, 0, (QH == 8 && N >= 512)>;
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
   Tw twr;
   tile_setup(twr, twtab, tw);
@@ -1166,12 +1180,15 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
 // another's kernel.  (As one pair of persistent kernels per length on graph
 // branches, 256 mixed frames took 372 us: the runtime put five branches on
 // three hardware queues, and the 1024-point class ran by itself behind the
-// 2048-point one, 120 us with most of the chip idle.)
-// Last-pass twiddles in the LDS table for the 5-register window and 4
-// wavefronts, which keeps the kernel at 3 wavefronts per SIMD; the others run 2
-// either way.
+// 2048-point one, 120 us with most of the chip idle; so they take 270.)
+// Last-pass twiddles in the LDS table for the narrow windows and 4 wavefronts,
+// which keeps the kernel at 3 wavefronts per SIMD; the others run 2 either way.
+// The narrow kernel's window is 7 registers up to 256 points (whose passes hold
+// fewer twiddles) and 5 above.
+template <int N, int QH>
+constexpr int merged_window() { return QH <= 5 && N <= 256 ? 7 : QH; }
 template <int N, int QH, int W>
-using BatchTw = FftTwiddles<N, 0, (QH <= 5 && W == 4)>;
+using BatchTw = FftTwiddles<N, 0, (QH < 8 && W == 4)>;
 
 template <int N, int QH, int W>
 __device__ __forceinline__ void batch_demod_length(const FrameDesc& d, const BatchIo& io, int t,
@@ -1196,12 +1213,12 @@ void batch_merged_demod_kernel(const FrameDesc* __restrict__ fd, const BatchTile
   const BatchTile t = tiles[blockIdx.x];
   const FrameDesc d = fd[t.frame];
   switch (d.N) {
-    case 64: batch_demod_length<64, QH, W>(d, io, t.at, tws.tw[0], lds, twtab); break;
-    case 128: batch_demod_length<128, QH, W>(d, io, t.at, tws.tw[1], lds, twtab); break;
-    case 256: batch_demod_length<256, QH, W>(d, io, t.at, tws.tw[2], lds, twtab); break;
-    case 512: batch_demod_length<512, QH, W>(d, io, t.at, tws.tw[3], lds, twtab); break;
-    case 1024: batch_demod_length<1024, QH, W>(d, io, t.at, tws.tw[4], lds, twtab); break;
-    default: batch_demod_length<2048, QH, W>(d, io, t.at, tws.tw[5], lds, twtab); break;
+    case 64: batch_demod_length<64, merged_window<64, QH>(), W>(d, io, t.at, tws.tw[0], lds, twtab); break;
+    case 128: batch_demod_length<128, merged_window<128, QH>(), W>(d, io, t.at, tws.tw[1], lds, twtab); break;
+    case 256: batch_demod_length<256, merged_window<256, QH>(), W>(d, io, t.at, tws.tw[2], lds, twtab); break;
+    case 512: batch_demod_length<512, merged_window<512, QH>(), W>(d, io, t.at, tws.tw[3], lds, twtab); break;
+    case 1024: batch_demod_length<1024, merged_window<1024, QH>(), W>(d, io, t.at, tws.tw[4], lds, twtab); break;
+    default: batch_demod_length<2048, merged_window<2048, QH>(), W>(d, io, t.at, tws.tw[5], lds, twtab); break;
   }
   __syncthreads();  // outputs written; the frame's last data symbol completes it
   if (threadIdx.x == 0 && atomicAdd(done_count + d.index, 1) == d.T - 2)
@@ -1225,12 +1242,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
   const BatchTile t = tiles[blockIdx.x];
   const FrameDesc d = fd[t.frame];
   switch (d.N) {
-    case 64: batch_estimate_length<64, QH, W, J>(d, io, t.at, tws.tw[0], lds); break;
-    case 128: batch_estimate_length<128, QH, W, J>(d, io, t.at, tws.tw[1], lds); break;
-    case 256: batch_estimate_length<256, QH, W, J>(d, io, t.at, tws.tw[2], lds); break;
-    case 512: batch_estimate_length<512, QH, W, J>(d, io, t.at, tws.tw[3], lds); break;
-    case 1024: batch_estimate_length<1024, QH, W, J>(d, io, t.at, tws.tw[4], lds); break;
-    default: batch_estimate_length<2048, QH, W, J>(d, io, t.at, tws.tw[5], lds); break;
+    case 64: batch_estimate_length<64, merged_window<64, QH>(), W, J>(d, io, t.at, tws.tw[0], lds); break;
+    case 128: batch_estimate_length<128, merged_window<128, QH>(), W, J>(d, io, t.at, tws.tw[1], lds); break;
+    case 256: batch_estimate_length<256, merged_window<256, QH>(), W, J>(d, io, t.at, tws.tw[2], lds); break;
+    case 512: batch_estimate_length<512, merged_window<512, QH>(), W, J>(d, io, t.at, tws.tw[3], lds); break;
+    case 1024: batch_estimate_length<1024, merged_window<1024, QH>(), W, J>(d, io, t.at, tws.tw[4], lds); break;
+    default: batch_estimate_length<2048, merged_window<2048, QH>(), W, J>(d, io, t.at, tws.tw[5], lds); break;
   }
 }
 
@@ -1275,7 +1292,7 @@ __global__ __launch_bounds__(64 * W) void fft_kernel(const uint32_t* __restrict_
   const int a0 = Sh::WPT > 1 ? a_wg : a_wg + ts - f;
   __shared__ float2 twtab[FftTwiddles<N>::kLdsFloat2 > 0 ? FftTwiddles<N>::kLdsFloat2 : 1];
   if constexpr (FftTwiddles<N>::kLdsLast) {
-    FftTwiddles<N>::P3Lds::fill(twtab, tw, threadIdx.x, blockDim.x);
+    FftTwiddles<N>::LastLds::fill(twtab, tw, threadIdx.x, blockDim.x);
     __syncthreads();
   }
   if (a0 >= A) return;  // uniform over whoever shares an exchange fence
@@ -1507,6 +1524,8 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
 }
 
 // Register-window tiers: the smallest instantiated QH >= ceil((U/2 + 1) / L).
+// 6 and 7 exist where a transform has at most 16 lanes, so that a register is
+// 4 to 16 bins and common subcarrier counts (52 of 64, 180 of 256) need them.
 template <int N>
 hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   constexpr int L = FftShape<N>::L;
@@ -1515,6 +1534,10 @@ hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t*
   if (need <= 2) return demod_qh<N, 2>(la, H, xhat, bits);
   if (need <= 4) return demod_qh<N, 4>(la, H, xhat, bits);
   if (need <= 5) return demod_qh<N, 5>(la, H, xhat, bits);
+  if constexpr (N <= 256) {
+    if (need <= 6) return demod_qh<N, 6>(la, H, xhat, bits);
+    if (need <= 7) return demod_qh<N, 7>(la, H, xhat, bits);
+  }
   if (need <= 8) return demod_qh<N, 8>(la, H, xhat, bits);
   return hipErrorInvalidValue;
 }
@@ -1751,7 +1774,7 @@ bool batch_kernels(int N, int max_u, int demod_waves, int est_jobs, int dem_sche
   }
 }
 
-int batch_window(int N, int U) { return (U / 2 + 1 + N / 16 - 1) / (N / 16); }
+bool batch_wide(int N, int U) { return (U / 2 + 1 + N / 16 - 1) / (N / 16) > (N <= 256 ? 7 : 5); }
 
 namespace {
 constexpr int kJobsMerged = 2;

@@ -92,8 +92,8 @@ bool batch_kernels(int N, int max_u, int demod_waves, int est_jobs, int dem_sche
 int fft_schedule_count(int N);
 void fft_schedule_radices(int N, int sched, int radices[3]);
 const void* batch_reset_func();
-// The merged kernels for frames whose spectrum window has batch_window(N, U)
-// <= 5 registers (wide = 0) or more (wide = 1), with `waves` (4 or 8)
+// The merged kernels for frames whose spectrum fits the narrow register window
+// (wide = 0) or does not (wide = 1, batch_wide), with `waves` (4 or 8)
 // wavefronts per demod workgroup.  By FFT length N = 64 << i: LDS of the
 // demod's exchange regions (lds_fft) and of its reduction rows per subcarrier
 // (lds_per_u), LDS and antennas of an estimate tile.
@@ -103,7 +103,7 @@ struct BatchMerged {
   size_t lds_fft[6] = {}, lds_per_u[6] = {}, est_lds[6] = {};
   int est_ants[6] = {};
 };
-int batch_window(int N, int U);
+bool batch_wide(int N, int U);
 BatchMerged batch_merged(bool wide, int waves);
 
 // ---- learned refinement of the channel estimate (rx_denoise.hip)
