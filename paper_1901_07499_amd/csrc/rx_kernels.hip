@@ -678,19 +678,19 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
 // reads in the antenna loop) where the kernel keeps its wavefronts per SIMD with
 // them -- N = 1024 and 2048 at the widest windows (3 at 5 registers, 2 at 8; the
 // 5-register kernels were measured faster), N <= 256 at up to 5 (3) and at 8 (2)
-// -- and in the LDS table elsewhere.  At N <= 256 with 6 or 7 registers the
-// table is what lets 3 fit (180 to 194 VGPRs without): 16 antennas x 64 points,
-// 52 subcarriers, 14 980 slots, 327 us in the 8-register kernel at 2 per SIMD,
-// 294 in the 7-register one at 3.  The N = 2048 kernel with the 5-register
+// -- and in the LDS table elsewhere.  With 6 or 7 registers the table is what
+// lets 3 fit (180 to 194 VGPRs without at N <= 256): 16 antennas x 64 points, 52
+// subcarriers, 14 980 slots, 327 us in the 8-register kernel at 2 per SIMD, 294 in
+// the 7-register one at 3.  The N = 2048 kernel with the 5-register
 // window needs a register budget of 3 wavefronts per SIMD to stay there (168
 // VGPRs; without the bound the compiler takes 169 and drops to 2).
 template <int N, int QH, int W = 4>
 constexpr bool demod_twiddles_in_lds() {
   if (W != 4) return false;
-  return N <= 256 ? QH == 6 || QH == 7 : N == 512 || QH < 5;
+  return QH == 6 || QH == 7 || N == 512 || (N > 512 && QH < 5);
 }
 template <int N, int QH, int W>
-constexpr int demod_min_waves() { return W == 8 ? 2 : N == 2048 && QH == 5 ? 3 : 1; }
+constexpr int demod_min_waves() { return W == 8 ? 2 : (N == 2048 && QH == 5) || QH == 6 || QH == 7 ? 3 : 1; }
 
 // Uniform slots: one workgroup per (slot, data symbol).
 template <int N, int QH, int W>
@@ -1520,12 +1520,15 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
       return demod_items_launch<N, QH, false, false>(la, H, xhat, bits, wa, lfa, grid, lds);
     }
   }
-  return demod_launch<N, QH, kWavesDemod>(la, H, xhat, bits);
+  if constexpr (Sh::F == 1) return demod_launch<N, QH, kWavesDemod>(la, H, xhat, bits);
+  return hipErrorInvalidValue;  // not reached: short transforms took the items kernel
 }
 
 // Register-window tiers: the smallest instantiated QH >= ceil((U/2 + 1) / L).
-// 6 and 7 exist where a transform has at most 16 lanes, so that a register is
-// 4 to 16 bins and common subcarrier counts (52 of 64, 180 of 256) need them.
+// 6 and 7 run 3 wavefronts per SIMD where 8 runs 2: 64 antennas, 600 slots, 700 of
+// 1024 subcarriers 726 us with 8 registers and 670 with 6, 1400 of 2048 1667 and
+// 1515, 360 of 512 382 and 344, 840 of 1024 741 and 701 with 7.  At 512 points 7
+// registers spill (390 and 469 us), at 2048 they gain nothing (1722 and 1738).
 template <int N>
 hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   constexpr int L = FftShape<N>::L;
@@ -1534,8 +1537,8 @@ hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t*
   if (need <= 2) return demod_qh<N, 2>(la, H, xhat, bits);
   if (need <= 4) return demod_qh<N, 4>(la, H, xhat, bits);
   if (need <= 5) return demod_qh<N, 5>(la, H, xhat, bits);
-  if constexpr (N <= 256) {
-    if (need <= 6) return demod_qh<N, 6>(la, H, xhat, bits);
+  if (need <= 6) return demod_qh<N, 6>(la, H, xhat, bits);
+  if constexpr (N <= 256 || N == 1024) {
     if (need <= 7) return demod_qh<N, 7>(la, H, xhat, bits);
   }
   if (need <= 8) return demod_qh<N, 8>(la, H, xhat, bits);

@@ -1,5 +1,5 @@
-"""Spectrum windows of the short transforms (6, 7 and 8 registers at 64 to 256 points) in calls that fill the GPU's
-multi-item kernel, and in a batch, against the FP64 oracle."""
+"""Spectrum windows of 6, 7 and 8 registers in calls past the small-call paths, and in a batch, against the FP64
+oracle."""
 import numpy as np
 import pytest
 
@@ -23,10 +23,11 @@ def rx():
 # the least and the greatest multiple of four subcarriers of each window
 @pytest.mark.parametrize("N,U", [(64, 40), (64, 44), (64, 48), (64, 52), (64, 56), (64, 60), (128, 80), (128, 92),
                                  (128, 96), (128, 108), (128, 112), (128, 124), (256, 160), (256, 188), (256, 192),
-                                 (256, 220), (256, 224), (256, 252)])
+                                 (256, 220), (256, 224), (256, 252), (512, 324), (512, 380), (512, 384), (512, 444), (1024, 644),
+                                 (1024, 764), (1024, 768), (1024, 892), (2048, 1284), (2048, 1532), (2048, 1536), (2048, 1788)])
 @pytest.mark.parametrize("A,cp_odd", [(3, 0), (10, 1)])
-def test_windows_of_short_transforms(rx, N, U, A, cp_odd):
-    S = 700                                        # past the split of a wavefront's slots over antennas
+def test_wide_windows(rx, N, U, A, cp_odd):
+    S = 700 if N < 512 else 90                     # past the split of a wavefront's slots over antennas
     cfg = C2.replace(n_ant=A, fft_len=N, cp_len=N // 16 + cp_odd, n_used=U, n_sym=4, bits_per_sym=4, n_slots=S)
     print("[case] window", N, U, A, cp_odd, flush=True)
     fr = make_frames(cfg, n_slots=2)
