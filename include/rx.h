@@ -158,7 +158,7 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
  * allocated.  The channel estimate is kept in a library-owned device array of
  * RX_NOALLOC_SCRATCH_BYTES on each GPU the library runs on, held until the
  * process ends, and the slots go through in chunks whose estimates fit it
- * (one launch pair per chunk; results equal rx_process_frame's).  One slot's
+ * (the kernels are chosen for the whole call; results equal rx_process_frame's).  One slot's
  * estimate, A*U*8 bytes, must fit, else RX_E_SCRATCH.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (different streams,
  * or host threads) race and must be serialised by the caller.  The array
