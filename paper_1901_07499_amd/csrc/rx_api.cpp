@@ -93,6 +93,7 @@ rx::LaunchArgs launch_args(rx_plan_t plan, const int16_t* iq, int64_t S, void* s
   la.U = plan->p.n_used;
   la.T = plan->p.n_sym;
   la.B = plan->p.bits_per_sym;
+  la.zf = plan->p.combiner == RX_COMB_ZF;
   la.tw = plan->tw;
   la.pf = plan->pf;
   la.ps = spacing(plan->p);

@@ -18,7 +18,9 @@
 //                  (Weighting inside the loop needs g first, a pass over every
 //                  channel row in series: a 13-antenna, 512-point, 150-slot
 //                  call took 34.8 us with it and takes 24.4 us without; the
-//                  error against 64 bits went from 1.0e-7 to 8.3e-8.)
+//                  error against 64 bits went from 1.0e-7 to 8.3e-8.  Where g
+//                  overflows or a channel is not finite the two differ: see
+//                  zf_past_plain.)
 //
 // After the FFT a lane holds bins li + L*q, q = 0..P-1 (see rx_fft.hpp).  The
 // used subcarriers are the bins within U/2 of DC, so only the registers
@@ -404,6 +406,27 @@ __device__ __forceinline__ float2 mrc_equalize(float2 z, float g) {
   return g > 0.f ? make_float2(z.x / g, z.y / g) : make_float2(0.f, 0.f);
 }
 
+// ZF where the channel energy g is not at most kZfPlain (2^126, past which its
+// reciprocal is subnormal).  The weights are conj(H) / g: g finite, a division;
+// g overflowed, finite channels weigh 0 (also where z overflowed with it) and
+// one that is not finite makes the symbol NaN.
+constexpr float kZfPlain = 8.50705917e37f;
+__device__ __forceinline__ float2 zf_past_plain(float2 z, float g, bool finite) {
+  if (g < __builtin_inff()) return make_float2(z.x / g, z.y / g);
+  const float v = finite ? 0.f : __builtin_nanf("");
+  return make_float2(v, v);
+}
+__device__ __forceinline__ bool is_finite(float2 h) {
+  return fabsf(h.x) < __builtin_inff() && fabsf(h.y) < __builtin_inff();
+}
+// Hd: the subcarrier's entry of antenna 0.
+__device__ __forceinline__ float2 zf_past_plain(float2 z, float g, const float2* __restrict__ Hd, int A, int U) {
+  bool finite = true;
+#pragma unroll 1
+  for (int a = 0; a < A; a++) finite = finite && is_finite(Hd[(int64_t)a * U]);
+  return zf_past_plain(z, g, finite);
+}
+
 // Sum of n partial sums get(w, z, g) in a fixed order: four chains of every
 // fourth term, then their sum.  Shorter chains round less than one (8 terms: an
 // 8-antenna call's error against 64 bits is 9.4e-8 summed one after another),
@@ -451,18 +474,18 @@ __device__ __forceinline__ void pack_codes(const uint8_t* codes, int n, int B, u
 }
 
 // Output of one data symbol by the whole workgroup of W wavefronts: sum(d, z,
-// g) gives the sums of subcarrier d; x = z / g (0 when g = 0), one thread per
+// g) gives the sums of subcarrier d; x = equalize(d, z, g), one thread per
 // subcarrier, then the decisions, whose codes meet in LDS (codes: U bytes and
 // 3 of slack, 4-byte aligned) and are packed MSB-first, one thread per four
 // (B/2 bytes).  xrow, brow: the symbol's output rows, or null.
-template <int W, typename SumF>
-__device__ __forceinline__ void finish_symbol(int U, int B, SumF sum, float2* __restrict__ xrow,
+template <int W, typename SumF, typename EqF>
+__device__ __forceinline__ void finish_symbol(int U, int B, SumF sum, EqF equalize, float2* __restrict__ xrow,
                                               uint8_t* __restrict__ brow, uint8_t* codes) {
   for (int d = threadIdx.x; d < U; d += 64 * W) {
     float2 zz = make_float2(0.f, 0.f);
     float gg = 0.f;
     sum(d, zz, gg);
-    const float2 x = mrc_equalize(zz, gg);
+    const float2 x = equalize(d, zz, gg);
     if (xrow) xrow[d] = x;
     codes[d] = (uint8_t)qam_code(x, B);
   }
@@ -479,6 +502,7 @@ struct SlotView {
   float2* xhat;        // [T-1][U]
   uint8_t* bits;       // [T-1][U*B/8]
   int A, T, CP, U, B;
+  bool zf;
 };
 
 // Demodulate data symbol t of one slot with the W wavefronts of the
@@ -670,6 +694,8 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
         gg += rg[w * U + d];
       }
     }
+  }, [&](int d, float2 zz, float gg) {
+    return sv.zf && !(gg <= kZfPlain) ? zf_past_plain(zz, gg, Hs + d, A, U) : mrc_equalize(zz, gg);
   }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
   reinterpret_cast<uint8_t*>(rg + ROWS * U));
 }
@@ -697,7 +723,7 @@ template <int N, int QH, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_min_waves<N, QH, W>())))
 void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int CP, int U, int B,
                   const float2* __restrict__ tw, const float2* __restrict__ H, float2* __restrict__ xhat,
-                  uint8_t* __restrict__ bits) {
+                  uint8_t* __restrict__ bits, int zf) {
   using Tw = FftTwiddles<N, 0, demod_twiddles_in_lds<N, QH, W>()>;
   extern __shared__ float2 lds[];
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
@@ -713,6 +739,7 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
   sv.xhat = xhat ? xhat + s * Td * (int64_t)U : nullptr;
   sv.bits = bits ? bits + s * Td * (int64_t)(U * B / 8) : nullptr;
   sv.A = A; sv.T = T; sv.CP = CP; sv.U = U; sv.B = B;
+  sv.zf = zf;
   demod_tile<N, QH, W>(sv, t, lds, twr);
 }
 
@@ -742,7 +769,7 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
                                                              const float2* __restrict__ tw,
                                                              const float2* __restrict__ H,
                                                              float2* __restrict__ xhat, uint8_t* __restrict__ bits,
-                                                             int Wa, int lfa_arg) {
+                                                             int Wa, int lfa_arg, int zf) {
   using Sh = FftShape<N>;
   static_assert(Sh::WPT == 1, "a transform within one wavefront");
   constexpr int NI = 2 * QH;
@@ -881,7 +908,8 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 
   // The workgroup's items are consecutive, so their x-hat rows and bit rows
   // are contiguous.  x-hat and the decision codes (to LDS) come straight from
-  // the registers when one transform slot holds an item; otherwise every slot's
+  // the registers when one transform slot holds an item (for ZF too, its rare
+  // look at the channel would cost the loop above a register); otherwise every slot's
   // partial sums go to its LDS row and one thread per subcarrier sums the
   // item's Wa Fa rows in a fixed order.  Then one thread per
   // four codes packs the bits.
@@ -892,8 +920,8 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
   float2* rz = lds;                                      // [ROWS][U]
   float* rg = reinterpret_cast<float*>(lds + ROWS * U);  // [ROWS][U]
   uint8_t* codes = reinterpret_cast<uint8_t*>(rg + ROWS * U);  // [nsub] (+ 4 bytes of slack)
-  if (step == 1) {
-    const int litem = wave * Sh::F + f;
+  if (step == 1 && !zf) {
+    const int litem = ts;
     if (litem < nitems) {
 #pragma unroll
       for (int i = 0; i < NI; i++) {
@@ -936,7 +964,12 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
           gg += rg[r];
         }
       }
-      const float2 x = mrc_equalize(zz, gg);
+      float2 x = mrc_equalize(zz, gg);
+      if (zf && !(gg <= kZfPlain)) {
+        int td = Td;
+        asm volatile("" : "+s"(td));  // a division anew: its reciprocal of Td is not held through the loop above
+        x = zf_past_plain(zz, gg, H + slot_of(item0 + litem, td) * A * U + d, A, U);
+      }
       if (xhat) xhat[item0 * U + v] = x;
       codes[v] = (uint8_t)qam_code(x, B);
       d += sr;
@@ -962,11 +995,15 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 // it; the pilot's transform is repeated for every data symbol, on compute
 // units that would idle.  With NB > 1 the groups' sums go to zp, gp and
 // small_finish_kernel adds them in group order.
+__device__ __forceinline__ float2 small_equalize(float2 z, float g, int zf) {
+  return zf && !(g <= kZfPlain) ? zf_past_plain(z, g, g > 0.f) : mrc_equalize(z, g);
+}
+
 template <int N, int QH, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void small_kernel(
     const uint32_t* __restrict__ iq, int A, int T, int CP, int U, int B, const float2* __restrict__ tw,
     const float2* __restrict__ pf, float2* __restrict__ xhat, uint8_t* __restrict__ bits, int NB,
-    float2* __restrict__ zp, float* __restrict__ gp) {
+    float2* __restrict__ zp, float* __restrict__ gp, int zf) {
   using Sh = FftShape<N>;
   using El = EstLane<N, QH>;
   constexpr int NI = El::NI, TPW = transforms_per_group<N, W>();
@@ -1031,6 +1068,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
         z[i].y = fmaf(h[i].x, y.y, fmaf(-h[i].y, y.x, z[i].y));
         g[i] = fmaf(h[i].x, h[i].x, fmaf(h[i].y, h[i].y, g[i]));
       }
+      if (zf) {  // a channel that is not finite makes the energy NaN, where finite ones overflow to infinity
+#pragma unroll
+        for (int i = 0; i < NI; i++) g[i] += (h[i].x - h[i].x) + (h[i].y - h[i].y);
+      }
     }
     exchange_fence<N>();
   }
@@ -1055,7 +1096,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
     }, zz, gg);
   };
   if (NB == 1) {
-    finish_symbol<W>(U, B, sum, xhat ? xhat + item * U : nullptr,
+    finish_symbol<W>(U, B, sum, [&](int, float2 zz, float gg) { return small_equalize(zz, gg, zf); },
+                     xhat ? xhat + item * U : nullptr,
                      bits ? bits + item * (int64_t)(U * B / 8) : nullptr, reinterpret_cast<uint8_t*>(rg + rows * U));
   } else {
     for (int d = threadIdx.x; d < U; d += 64 * W) {
@@ -1074,7 +1116,7 @@ constexpr int kWavesFinish = 4;
 __global__ __launch_bounds__(64 * kWavesFinish) void small_finish_kernel(const float2* __restrict__ zp,
                                                                         const float* __restrict__ gp, int NB, int Td,
                                                                         int U, int B, float2* __restrict__ xhat,
-                                                                        uint8_t* __restrict__ bits) {
+                                                                        uint8_t* __restrict__ bits, int zf) {
   constexpr int kSeg = 64 * kWavesFinish;
   __shared__ uint32_t codes[kSeg / 4 + 1];
   const int segs = (U + kSeg - 1) / kSeg, d0 = blockIdx.x % segs * kSeg;
@@ -1084,7 +1126,7 @@ __global__ __launch_bounds__(64 * kWavesFinish) void small_finish_kernel(const f
       p = zp[(item * NB + b) * U + d0 + d];
       q = gp[(s * NB + b) * U + d0 + d];
     }, zz, gg);
-  }, xhat ? xhat + item * U + d0 : nullptr, bits ? bits + (item * U + d0) * B / 8 : nullptr,
+  }, [&](int, float2 zz, float gg) { return small_equalize(zz, gg, zf); }, xhat ? xhat + item * U + d0 : nullptr, bits ? bits + (item * U + d0) * B / 8 : nullptr,
   reinterpret_cast<uint8_t*>(codes));
 }
 
@@ -1167,6 +1209,7 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
     sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
     sv.bits = io.bits ? io.bits + d.b_off : nullptr;
     sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
+    sv.zf = false;
     demod_tile<N, QH, W>(sv, 1 + tile - d.dem_tile0, lds, twr);
     __syncthreads();  // outputs written and LDS free before the next tile
     done_index = d.index;
@@ -1201,6 +1244,7 @@ __device__ __forceinline__ void batch_demod_length(const FrameDesc& d, const Bat
   sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
   sv.bits = io.bits ? io.bits + d.b_off : nullptr;
   sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
+  sv.zf = false;
   demod_tile<N, QH, W>(sv, t, lds, twr);
 }
 
@@ -1454,7 +1498,7 @@ hipError_t demod_items_launch(const LaunchArgs& la, const float2* H, float2* xha
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((demod_items_kernel<N, QH, kWavesDemod, STAGED, SPLIT>), dim3((unsigned)grid),
                      dim3(64 * kWavesDemod), lds, la.stream, la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H,
-                     xhat, bits, wa, lfa);
+                     xhat, bits, wa, lfa, (int)la.zf);
   return hipGetLastError();
 }
 
@@ -1472,7 +1516,7 @@ hipError_t demod_launch(const LaunchArgs& la, const float2* H, float2* xhat, uin
   hipError_t e = allow_lds(demod_kernel<N, QH, W>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((demod_kernel<N, QH, W>), dim3((unsigned)(la.S * (la.T - 1))), dim3(64 * W), lds, la.stream,
-                     la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits);
+                     la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits, (int)la.zf);
   return hipGetLastError();
 }
 
@@ -1592,11 +1636,12 @@ hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* x
   hipError_t e = allow_lds(small_kernel<N, QH, W>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((small_kernel<N, QH, W>), dim3((unsigned)(items * NB)), dim3(64 * W), lds, la.stream, la.iq,
-                     la.A, la.T, la.CP, la.U, la.B, la.tw, la.pf, xhat, bits, NB, zp, gp);
+                     la.A, la.T, la.CP, la.U, la.B, la.tw, la.pf, xhat, bits, NB, zp, gp, (int)la.zf);
   if ((e = hipGetLastError()) != hipSuccess || NB == 1) return e;
   const int segs = (la.U + 64 * kWavesFinish - 1) / (64 * kWavesFinish);
   hipLaunchKernelGGL(small_finish_kernel, dim3((unsigned)(items * segs)), dim3(64 * kWavesFinish), 0, la.stream,
-                     (const float2*)zp, (const float*)gp, NB, la.T - 1, la.U, la.B, xhat, bits);
+                     (const float2*)zp, (const float*)gp, NB, la.T - 1, la.U, la.B, xhat, bits,
+                     (int)la.zf);
   return hipGetLastError();
 }
 

@@ -14,6 +14,7 @@ struct LaunchArgs {
   int64_t S;       // slots of this launch
   int64_t S_call;  // and of the call it is part of (the kernel choice goes by these)
   int A, N, CP, U, T, B;
+  bool zf;             // combiner: ZF, else MRC
   const float2* tw;    // tw[k] = exp(-2 pi i k / N), k < N
   const float2* pf;    // pf[d] = conj(Xp[d]) / |Xp[d]|^2 (pilot subcarriers only)
   int ps;              // pilot spacing: 1 = block pilot, > 1 = comb on d % ps == 0
