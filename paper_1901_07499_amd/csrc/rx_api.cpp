@@ -208,7 +208,7 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
   if ((st = check_device(plan)) != RX_OK) return st;
   const rx::LaunchArgs la = launch_args(plan, iq, n_slots, hip_stream);
   float2* x2 = reinterpret_cast<float2*>(xhat);
-  if (!H) return hip_status(rx::launch_frame(la, static_cast<float2*>(workspace), x2, bits));
+  if (!H) return hip_status(rx::launch_frame(la, static_cast<float2*>(workspace), x2, bits, true));
   float2* H2 = reinterpret_cast<float2*>(H);
   if ((st = hip_status(rx::launch_estimate(la, H2))) != RX_OK) return st;
   return hip_status(rx::launch_demod(la, H2, x2, bits));
@@ -264,7 +264,7 @@ int process_frame_in(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
     la.S_call = n_slots;
     float2* x = xhat ? reinterpret_cast<float2*>(xhat) + s0 * Td * plan->p.n_used : nullptr;
     uint8_t* b = bits ? bits + s0 * Td * row_bytes : nullptr;
-    if ((st = hip_status(rx::launch_frame(la, hbuf, x, b))) != RX_OK) return st;
+    if ((st = hip_status(rx::launch_frame(la, hbuf, x, b, false))) != RX_OK) return st;
   }
   return RX_OK;
 }

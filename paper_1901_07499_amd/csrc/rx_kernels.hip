@@ -990,11 +990,12 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 // The whole path of few items in one kernel: workgroup = (slot, data symbol,
 // one of NB groups of the antennas).  A transform takes the pilot symbol of its
 // antenna, keeps the LS estimate of the window's subcarriers in registers (the
-// products the estimate kernel stores) and goes on to the antenna's data
-// symbol, so no estimate goes through memory and no second kernel waits for
-// it; the pilot's transform is repeated for every data symbol, on compute
-// units that would idle.  With NB > 1 the groups' sums go to zp, gp and
-// small_finish_kernel adds them in group order.
+// estimate kernel's, but for where the compiler fuses a product and a sum) and
+// goes on to the antenna's data symbol, so no second kernel waits for an
+// estimate in memory; the pilot's transform is repeated for every data symbol,
+// on compute units that would idle.  Hout, if not null, receives the estimate (NB == 1).
+// With NB > 1 the groups' sums go to zp, gp and small_finish_kernel adds them in
+// group order.
 __device__ __forceinline__ float2 small_equalize(float2 z, float g, int zf) {
   return zf && !(g <= kZfPlain) ? zf_past_plain(z, g, g > 0.f) : mrc_equalize(z, g);
 }
@@ -1003,7 +1004,7 @@ template <int N, int QH, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void small_kernel(
     const uint32_t* __restrict__ iq, int A, int T, int CP, int U, int B, const float2* __restrict__ tw,
     const float2* __restrict__ pf, float2* __restrict__ xhat, uint8_t* __restrict__ bits, int NB,
-    float2* __restrict__ zp, float* __restrict__ gp, int zf) {
+    float2* __restrict__ zp, float* __restrict__ gp, float2* __restrict__ Hout, int zf) {
   using Sh = FftShape<N>;
   using El = EstLane<N, QH>;
   constexpr int NI = El::NI, TPW = transforms_per_group<N, W>();
@@ -1053,6 +1054,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
     unpack_symbol<N>(v[0], nxt);
     if (!odd) load_symbol<N>(nxt, rec(k) + to_data, li, true);
     else if (k0 + TPW + lead < na) load_symbol<N>(nxt, rec(k + TPW), li, true);
+    // (here, so that the data symbol's transform runs while the stores finish: the next wait for samples waits for
+    // them too)
+    if (odd && Hout && t == 1 && k < na) {
+      float2* hrow = Hout + (s * A + a0 + k) * (int64_t)U;
+#pragma unroll
+      for (int i = 0; i < NI; i++)
+        if (el.dq[i] >= 0) hrow[el.dq[i]] = h[i];
+    }
     fft_in_regs<N, 1>(v, buf, li, twr);
     if (!odd) {
 #pragma unroll
@@ -1626,7 +1635,7 @@ hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uin
 
 namespace {
 template <int N, int QH>
-hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits) {
+hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits, bool keep) {
   constexpr int W = kWavesSmall, TPW = transforms_per_group<N, W>();
   const int64_t items = la.S * (la.T - 1);
   const int na = (la.A + NB - 1) / NB;
@@ -1636,7 +1645,8 @@ hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* x
   hipError_t e = allow_lds(small_kernel<N, QH, W>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((small_kernel<N, QH, W>), dim3((unsigned)(items * NB)), dim3(64 * W), lds, la.stream, la.iq,
-                     la.A, la.T, la.CP, la.U, la.B, la.tw, la.pf, xhat, bits, NB, zp, gp, (int)la.zf);
+                     la.A, la.T, la.CP, la.U, la.B, la.tw, la.pf, xhat, bits, NB, zp, gp,
+                     keep && NB == 1 ? scratch : nullptr, (int)la.zf);
   if ((e = hipGetLastError()) != hipSuccess || NB == 1) return e;
   const int segs = (la.U + 64 * kWavesFinish - 1) / (64 * kWavesFinish);
   hipLaunchKernelGGL(small_finish_kernel, dim3((unsigned)(items * segs)), dim3(64 * kWavesFinish), 0, la.stream,
@@ -1646,12 +1656,12 @@ hipError_t small_launch(const LaunchArgs& la, int NB, float2* scratch, float2* x
 }
 
 template <int N>
-hipError_t small_n(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits) {
+hipError_t small_n(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, uint8_t* bits, bool keep) {
   constexpr int L = FftShape<N>::L;
   const int need = (la.U / 2 + 1 + L - 1) / L;
-  if (need <= 2) return small_launch<N, 2>(la, NB, scratch, xhat, bits);
-  if (need <= 5) return small_launch<N, 5>(la, NB, scratch, xhat, bits);
-  if (need <= 8) return small_launch<N, 8>(la, NB, scratch, xhat, bits);
+  if (need <= 2) return small_launch<N, 2>(la, NB, scratch, xhat, bits, keep);
+  if (need <= 5) return small_launch<N, 5>(la, NB, scratch, xhat, bits, keep);
+  if (need <= 8) return small_launch<N, 8>(la, NB, scratch, xhat, bits, keep);
   return hipErrorInvalidValue;
 }
 }  // namespace
@@ -1660,11 +1670,12 @@ hipError_t small_n(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, 
 // costs two transforms per antenna where the two kernels cost one, and saves
 // the estimate kernel (about the time of three transforms in a row); several
 // groups shorten the row of transforms but add the finishing kernel (about
-// two).  The groups' sums share the A U 8 bytes per slot that the estimate
-// would have taken.  One slot, this path against the two kernels with 8
-// wavefronts (and with 4): 8 antennas x 64 points 8.1 us against 10.8 (11.8),
-// 64 x 1024 16.2 against 25.1 (33.6), 128 x 2048 30.8 against 114 (155);
-// towards the line they meet: 64 x 1024, 8 slots, 25.1 against 27.2.
+// two) and, as their sums lie in the A U 8 bytes per slot that hold the estimate
+// afterwards, the estimate kernel behind it (which the call without a caller's
+// workspace leaves out; it takes the same groups, so the same bits).  One slot,
+// this path against the two kernels: 8 antennas x 64 points 6.6 us against 9.1,
+// 64 x 1024 20.8 (16.3 without the estimate behind it) against 25.4, 128 x 512
+// 17.3 against 25.9, 128 x 2048 46.6 against 117.
 int small_groups(const LaunchArgs& la) {
   const int64_t Td = la.T - 1, items = la.S_call * Td;
   if (la.fft_mode != 0 || la.ps > 1 || items > kSmallItems) return 0;
@@ -1674,23 +1685,27 @@ int small_groups(const LaunchArgs& la) {
   if (nb > most) nb = most;
   if (nb > kSmallItems / items) nb = (int)(kSmallItems / items);
   if (nb < 1) nb = 1;
-  const int rounds = ((la.A + nb - 1) / nb + per_wg - 1) / per_wg;
-  return 2 * rounds + (nb > 1 ? 2 : 0) < most + 3 ? nb : 0;
+  const auto cost = [&](int n) { return 2 * (((la.A + n - 1) / n + per_wg - 1) / per_wg) + (n > 1 ? 5 : 0); };
+  if (cost(1) <= cost(nb)) nb = 1;
+  return cost(nb) < most + 3 ? nb : 0;
 }
 
-hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits) {
+hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits, bool keep) {
+  hipError_t e;
   if (const int nb = small_groups(la)) {
     switch (la.N) {
-      case 64: return small_n<64>(la, nb, scratch, xhat, bits);
-      case 128: return small_n<128>(la, nb, scratch, xhat, bits);
-      case 256: return small_n<256>(la, nb, scratch, xhat, bits);
-      case 512: return small_n<512>(la, nb, scratch, xhat, bits);
-      case 1024: return small_n<1024>(la, nb, scratch, xhat, bits);
-      case 2048: return small_n<2048>(la, nb, scratch, xhat, bits);
+      case 64: e = small_n<64>(la, nb, scratch, xhat, bits, keep); break;
+      case 128: e = small_n<128>(la, nb, scratch, xhat, bits, keep); break;
+      case 256: e = small_n<256>(la, nb, scratch, xhat, bits, keep); break;
+      case 512: e = small_n<512>(la, nb, scratch, xhat, bits, keep); break;
+      case 1024: e = small_n<1024>(la, nb, scratch, xhat, bits, keep); break;
+      case 2048: e = small_n<2048>(la, nb, scratch, xhat, bits, keep); break;
       default: return hipErrorInvalidValue;
     }
+    // the groups' sums lay where the estimate belongs
+    return e != hipSuccess || nb == 1 || !keep ? e : launch_estimate(la, scratch);
   }
-  const hipError_t e = launch_estimate(la, scratch);
+  e = launch_estimate(la, scratch);
   return e != hipSuccess ? e : launch_demod(la, scratch, xhat, bits);
 }
 

@@ -31,9 +31,9 @@ hipError_t launch_estimate(const LaunchArgs& la, float2* H);
 hipError_t launch_g(const LaunchArgs& la, const float2* H, float* g);
 // Both combiners: with one user ZF is MRC normalised by the channel energy.
 hipError_t launch_demod(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits);
-// The whole path without an estimate for the caller; scratch: A U 8 bytes per
-// slot.
-hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits);
+// The whole path in A U 8 bytes of scratch per slot, which hold the estimate
+// afterwards if `keep`.
+hipError_t launch_frame(const LaunchArgs& la, float2* scratch, float2* xhat, uint8_t* bits, bool keep);
 hipError_t launch_fft(const LaunchArgs& la, float2* Y);
 // rx_process_frame with the estimate in a fixed buffer, slots in chunks that
 // fit it (rx_api.cpp); returns an rx_status.

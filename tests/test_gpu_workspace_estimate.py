@@ -1,0 +1,42 @@
+"""rx_process_frame without H leaves the channel estimate in the workspace, on every path of small and large calls, so
+the caller can go on with it as H."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rx():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_1901_07499_amd import rx as mod
+    return mod
+
+
+# one workgroup per item with idle and with full transform slots, several rounds of them; several groups of antennas,
+# an uneven last one; ZF; a comb pilot; two kernels; and a call past the small ones
+@pytest.mark.parametrize("A,N,U,T,S,zf,ps", [
+    (1, 64, 52, 2, 1, 0, 1), (8, 64, 52, 11, 1, 0, 1), (130, 64, 60, 3, 2, 1, 1), (16, 128, 72, 14, 3, 0, 1),
+    (13, 512, 300, 8, 2, 0, 1), (64, 1024, 600, 14, 1, 0, 1), (64, 1024, 600, 14, 1, 1, 1), (127, 1024, 900, 5, 2, 0, 1),
+    (128, 2048, 1200, 14, 1, 0, 1), (9, 2048, 1700, 5, 1, 0, 1), (24, 1024, 600, 14, 2, 0, 1),
+    (64, 1024, 600, 14, 1, 0, 4), (16, 1024, 600, 14, 30, 0, 1)])
+def test_workspace_holds_the_estimate(rx, A, N, U, T, S, zf, ps):
+    print("[case] workspace", A, N, U, T, S, zf, ps, flush=True)
+    CP = N // 16
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    iq = torch.randint(-9000, 9001, (S, T, A, CP + N, 2), generator=gen, device="cuda", dtype=torch.int16)
+    pilot = np.exp(2j * np.pi * np.random.default_rng(4).random(U))
+    plan = rx.Plan(A, N, CP, U, T, 4, pilot, combiner=zf, pilot_spacing=ps)
+    need = plan.workspace_bytes(S)
+    assert need == S * A * U * 8
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    plan.process(iq, workspace=ws)
+    H = plan.estimate(iq)
+    torch.cuda.synchronize()
+    kept = ws[:need].view(torch.float32).view(H.shape)
+    # transforms of kernels that round apart: log2(N) half ulps of the largest bin each
+    assert ((kept - H).abs() <= 2 * np.log2(N) * 2.0 ** -24 * H.abs().amax()).all()
+    assert (ws[need:] == 0xFF).all()
