@@ -148,6 +148,10 @@ int rx_demod(rx_plan_t plan, const int16_t* iq, const float* H, int64_t n_slots,
 /* The whole path for S slots: rx_estimate followed by rx_demod on one stream.
  * H optional: when NULL the estimate is kept in `workspace`
  * (>= rx_workspace_bytes(plan, n_slots) bytes, 256-byte aligned).
+ * With H the results are those of the two calls bit for bit.  Without H a call
+ * of few slots may transform the pilots and sum the antennas in other kernels:
+ * its estimate, x-hat and decisions at a threshold agree within rounding.
+ * Asking for xhat, bits or both does not change either.
  * xhat and bits optional but not both NULL. */
 int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* H, float* xhat,
                      uint8_t* bits, void* workspace, void* hip_stream);
@@ -155,14 +159,15 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the whole
  * path of rx_process_frame without H or workspace arguments; nothing is
- * allocated.  The channel estimate is kept in a library-owned device array of
- * RX_NOALLOC_SCRATCH_BYTES on each GPU the library runs on, held until the
- * process ends, and the slots go through in chunks whose estimates fit it
- * (the kernels are chosen for the whole call; results equal rx_process_frame's).  One slot's
+ * allocated.  A library-owned device array of RX_NOALLOC_SCRATCH_BYTES on each
+ * GPU the library runs on, held until the process ends, takes the place of the
+ * workspace, and the slots go through in chunks whose estimates fit it (the
+ * kernels are chosen for the whole call; xhat and bits are those of
+ * rx_process_frame without H bit for bit).  One slot's
  * estimate, A*U*8 bytes, must fit, else RX_E_SCRATCH.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (different streams,
  * or host threads) race and must be serialised by the caller.  The array
- * needs no clearing (each chunk's estimate is written before it is read).
+ * needs no clearing (a chunk reads only what it has written).
  * xhat and bits optional but not both NULL. */
 #define RX_NOALLOC_SCRATCH_BYTES (64u << 20)
 int rx_process_frame_noalloc(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* xhat, uint8_t* bits,
