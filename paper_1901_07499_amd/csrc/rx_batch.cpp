@@ -5,9 +5,11 @@
 // Two merged kernel pairs serve the batch: frames whose spectrum fits the
 // narrow register window share an estimate and a demod kernel over all
 // FFT lengths, wider ones another pair; a workgroup is a tile, longest first.
-// One graph holds a reset node (clears queues and counters, stamps the start), the estimate nodes
-// beside it and the demod nodes after both, so one graph launch processes the
-// whole batch.
+// One graph holds a reset node (clears queues and counters, stamps the start)
+// and behind it a branch of estimate and demod node per pair, so one graph
+// launch processes the whole batch.  (Completion times count from the stamp, so
+// the estimates wait for it; beside it they also cost a join of two queues:
+// two 64-point frames took 35 us, 22 in a row.)
 // Frames with the same FFT length also form a class with its own kernels and
 // launch configuration (workgroup shapes and the FFT's radix schedule, chosen
 // separately for the estimate and demod kernels).  Once a class's
@@ -333,9 +335,8 @@ int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
       ep.blockDim = dim3(g.k.est_block);
       dp.blockDim = dim3(g.k.dem_block);
       hipGraphNode_t en, dn;
-      if (hipGraphAddKernelNode(&en, b->graph, nullptr, 0, &ep) != hipSuccess) return RX_E_HIP;
-      const hipGraphNode_t before[] = {en, reset};
-      if (hipGraphAddKernelNode(&dn, b->graph, before, 2, &dp) != hipSuccess) return RX_E_HIP;
+      if (hipGraphAddKernelNode(&en, b->graph, &reset, 1, &ep) != hipSuccess) return RX_E_HIP;
+      if (hipGraphAddKernelNode(&dn, b->graph, &en, 1, &dp) != hipSuccess) return RX_E_HIP;
     }
   }
   for (size_t ci = 0; ci < b->cls.size() && !merged(b); ci++) {

@@ -1278,8 +1278,7 @@ void batch_merged_demod_kernel(const FrameDesc* __restrict__ fd, const BatchTile
     done_time[d.index] = __builtin_amdgcn_s_memrealtime();
 }
 
-// Estimate: workgroup = tile, the longest first; it starts beside the reset
-// kernel.
+// Estimate: workgroup = tile, the longest first.
 template <int N, int QH, int W, int J>
 __device__ __forceinline__ void batch_estimate_length(const FrameDesc& d, const BatchIo& io, int a_wg,
                                                       const float2* __restrict__ tw, float2* lds) {
