@@ -1233,14 +1233,30 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
 // branches, 256 mixed frames took 372 us: the runtime put five branches on
 // three hardware queues, and the 1024-point class ran by itself behind the
 // 2048-point one, 120 us with most of the chip idle; so they take 270.)
-// Last-pass twiddles in the LDS table for the narrow windows and 4 wavefronts,
-// which keeps the kernel at 3 wavefronts per SIMD; the others run 2 either way.
+// Last-pass twiddles in the LDS table for the narrow windows and 4 wavefronts up
+// to 512 points, which keeps the kernel at 3 wavefronts per SIMD (59 VGPRs spill
+// without); the others run 2 either way.  At 1024 and 2048 points registers do (2
+// spill): a table that long is filled for every tile, and with the reduction rows
+// of a 64-point frame (40 KB) it exceeds a third of the LDS.  Table against
+// registers: 400 frames of 64 x 2048 1026 and 948 us (979 as persistent kernels
+// of their own), 256 frames of 64 x 64 and 64 x 2048 400 and 355, 4000 of 8 x 64
+// 522 and 370.
 // The narrow kernel's window is 7 registers up to 256 points (whose passes hold
 // fewer twiddles) and 5 above.
 template <int N, int QH>
 constexpr int merged_window() { return QH <= 5 && N <= 256 ? 7 : QH; }
 template <int N, int QH, int W>
-using BatchTw = FftTwiddles<N, 0, (QH < 8 && W == 4)>;
+using BatchTw = FftTwiddles<N, 0, (QH < 8 && W == 4 && N < 1024)>;
+// Entries of the longest table.
+template <int QH, int W>
+constexpr int batch_tw_entries() {
+  int m = 1;
+  for (int n : {BatchTw<64, merged_window<64, QH>(), W>::kLdsFloat2, BatchTw<128, merged_window<128, QH>(), W>::kLdsFloat2,
+                BatchTw<256, merged_window<256, QH>(), W>::kLdsFloat2, BatchTw<512, QH, W>::kLdsFloat2,
+                BatchTw<1024, QH, W>::kLdsFloat2, BatchTw<2048, QH, W>::kLdsFloat2})
+    m = n > m ? n : m;
+  return m;
+}
 
 template <int N, int QH, int W>
 __device__ __forceinline__ void batch_demod_length(const FrameDesc& d, const BatchIo& io, int t,
@@ -1262,7 +1278,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(QH <= 5 
 void batch_merged_demod_kernel(const FrameDesc* __restrict__ fd, const BatchTile* __restrict__ tiles, BatchIo io,
                                BatchTwiddles tws, int* done_count, unsigned long long* done_time) {
   extern __shared__ float2 lds[];
-  __shared__ float2 twtab[BatchTw<2048, QH, W>::kLdsFloat2 + 1];
+  __shared__ float2 twtab[batch_tw_entries<QH, W>()];
   const BatchTile t = tiles[blockIdx.x];
   const FrameDesc d = fd[t.frame];
   switch (d.N) {
