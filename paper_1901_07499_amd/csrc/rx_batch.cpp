@@ -301,6 +301,22 @@ void reset_args(rx_batch_s* b, ResetArgs& r) {
   std::copy(std::begin(p), std::end(p), r.ptrs);
 }
 
+// A kernel's nodes over n tiles, behind *last and each behind the one before: a
+// launch holds fewer than 2^32 threads.  *tiles is the kernel argument that
+// kp.kernelParams points to.
+int add_tiles(rx_batch_s* b, hipKernelNodeParams& kp, const rx::BatchTile* first, int n, const rx::BatchTile** tiles,
+              hipGraphNode_t* last) {
+  const int most = (int)(0xffffffffu / kp.blockDim.x);
+  for (int i = 0; i < n; i += std::min(most, n - i)) {
+    *tiles = first + i;
+    kp.gridDim = dim3(std::min(most, n - i));
+    hipGraphNode_t node;
+    if (hipGraphAddKernelNode(&node, b->graph, last, 1, &kp) != hipSuccess) return RX_E_HIP;
+    *last = node;
+  }
+  return RX_OK;
+}
+
 int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
   drop_graph(b);
   if (hipGraphCreate(&b->graph, 0) != hipSuccess) return RX_E_HIP;
@@ -321,22 +337,22 @@ int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
     for (size_t gi = 0; gi < b->groups.size(); gi++) {
       BatchGroup& g = b->groups[gi];
       rx::BatchIo gio = io;
-      void* ea[] = {&g.d_desc, &g.d_est, &gio, &tws};
-      void* da[] = {&g.d_desc, &g.d_dem, &gio, &tws, &b->d_done_count, &b->d_done_time};
+      const rx::BatchTile* tiles;
+      void* ea[] = {&g.d_desc, &tiles, &gio, &tws};
+      void* da[] = {&g.d_desc, &tiles, &gio, &tws, &b->d_done_count, &b->d_done_time};
       hipKernelNodeParams ep{}, dp{};
       ep.func = const_cast<void*>(g.k.est);
-      ep.gridDim = dim3(g.n_est);
       ep.sharedMemBytes = (unsigned)g.est_lds;
       ep.kernelParams = ea;
       dp.func = const_cast<void*>(g.k.dem);
-      dp.gridDim = dim3(g.n_dem);
       dp.sharedMemBytes = (unsigned)g.dem_lds;
       dp.kernelParams = da;
       ep.blockDim = dim3(g.k.est_block);
       dp.blockDim = dim3(g.k.dem_block);
-      hipGraphNode_t en, dn;
-      if (hipGraphAddKernelNode(&en, b->graph, &reset, 1, &ep) != hipSuccess) return RX_E_HIP;
-      if (hipGraphAddKernelNode(&dn, b->graph, &en, 1, &dp) != hipSuccess) return RX_E_HIP;
+      hipGraphNode_t last = reset;
+      if (add_tiles(b, ep, g.d_est, g.n_est, &tiles, &last) != RX_OK ||
+          add_tiles(b, dp, g.d_dem, g.n_dem, &tiles, &last) != RX_OK)
+        return RX_E_HIP;
     }
   }
   for (size_t ci = 0; ci < b->cls.size() && !merged(b); ci++) {

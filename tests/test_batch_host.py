@@ -67,3 +67,15 @@ def test_every_kernel_follows_the_reset(lib, frames):
         if n["kernel"] in MERGED_DEM:               # every demod waits for an estimate kernel of its frames
             assert any(nodes[d]["kernel"] == n["kernel"] - MERGED_DEM[0] + MERGED_EST[0] for d in n["deps"])
     b.close()
+
+
+@pytest.mark.parametrize("frames,T,demods", [(65536, 256, 1), (65536, 257, 2), (65536, 600, 3)])
+def test_launches_hold_fewer_threads_than_the_runtime_takes(lib, frames, T, demods):
+    b = Batch(lib, [(1, 64, 4, T)] * frames)
+    nodes = [n for n in b.process() if n["kernel"] in MERGED_DEM]
+    assert len(nodes) == demods
+    assert all(0 < n["grid"] * n["block"] < 1 << 32 for n in nodes)
+    assert sum(n["grid"] for n in nodes) == frames * (T - 1)
+    for p, n in zip(nodes, nodes[1:]):              # the tiles continue where the launch before ended
+        assert n["tiles"] == p["tiles"] + 8 * p["grid"]
+    b.close()
