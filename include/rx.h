@@ -186,12 +186,13 @@ int rx_debug_fft(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* Y, v
  * h_off[i] complex entries of the H buffer ([A][U]), its x-hat at x_off[i]
  * complex entries ([T-1][U]) and its bits at b_off[i] bytes ([T-1][U*b/8]).
  * The path per frame is the one of rx_process_frame (paper Sec. II-B and
- * II-C); the batch runs it for every frame in one graph launch.  At the
- * default configuration one estimate and one demod kernel (a second pair where
- * some spectra are much wider) serve every FFT length, the frames with the most
- * samples first.  Once a length has another configuration, each length has its
- * own persistent kernels that take tiles from device work queues (frames with
- * more antennas first, ties in batch order) on independent graph branches.
+ * II-C); the batch runs it for every frame in one graph launch.  One estimate
+ * and one demod kernel (a second pair where some spectra are much wider) serve
+ * every FFT length, the frames with the most samples first.  Once
+ * rx_batch_set_config has set a length's configuration, or rx_batch_autotune has
+ * found one faster, each length has its own persistent kernels instead that take
+ * tiles from device work queues (frames with more antennas first, ties in batch
+ * order) on independent graph branches.
  * ------------------------------------------------------------------------- */
 typedef struct rx_batch_s* rx_batch_t;
 
@@ -226,27 +227,30 @@ int rx_batch_process(rx_batch_t batch, const int16_t* iq, float* H, float* xhat,
  * class by class from the longest, within the whole batch graph with the
  * other classes as chosen so far: every shape with the class's schedules,
  * then every pair of schedules with the best shape, a choice replaced only
- * by one more than 1 % faster; at the end the default configuration, with its
- * kernels over all lengths, stays unless the chosen ones are more than 1 %
- * faster.  The whole batch runs 16 times first, untimed.
+ * by one more than 1 % faster; at the end the kernels over all lengths run
+ * unless the chosen ones are more than 1 % faster.  The whole batch runs 16
+ * times first, untimed.
  * Synchronous; overwrites the outputs. */
 int rx_batch_autotune(rx_batch_t batch, const int16_t* iq, float* H, float* xhat, uint8_t* bits,
                       void* workspace, int32_t reps, void* hip_stream);
 
 /* Configuration in use for the class of FFT length fft_len: wavefronts per
- * demod workgroup and jobs per estimate wavefront. */
+ * demod workgroup and jobs per estimate wavefront (those of the kernels over all
+ * lengths while these run). */
 int rx_batch_config(rx_batch_t batch, int32_t fft_len, int32_t* demod_waves, int32_t* est_jobs);
 
 /* Radix schedules in use for the class of FFT length fft_len: of the demod
  * kernel's transforms and of the estimate kernel's (indices as in
- * rx_fft_radices).  RX_E_INVALID_ARG if the batch has no such class. */
+ * rx_fft_radices; 0 in the kernels over all lengths).  RX_E_INVALID_ARG if the batch has no such class. */
 int rx_batch_schedules(rx_batch_t batch, int32_t fft_len, int32_t* dem_sched, int32_t* est_sched);
 
 /* Set the configuration of the class of FFT length fft_len instead of tuning
  * it: demod_waves and est_jobs in {2, 4, 8}, schedules below the count
  * rx_fft_radices accepts for fft_len.  The batch's current device only;
  * RX_E_INVALID_ARG for anything else (the configuration is then unchanged).
- * The next rx_batch_process rebuilds its graph. */
+ * From then on every length runs its own kernels, a length never set those of
+ * 4 wavefronts, 4 jobs and schedules 0.  The next rx_batch_process rebuilds its
+ * graph. */
 int rx_batch_set_config(rx_batch_t batch, int32_t fft_len, int32_t demod_waves, int32_t est_jobs,
                         int32_t dem_sched, int32_t est_sched);
 

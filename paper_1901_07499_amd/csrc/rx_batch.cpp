@@ -12,12 +12,12 @@
 // two 64-point frames took 35 us, 22 in a row.)
 // Frames with the same FFT length also form a class with its own kernels and
 // launch configuration (workgroup shapes and the FFT's radix schedule, chosen
-// separately for the estimate and demod kernels).  Once a class's
-// configuration differs from the default, the graph is one two-node branch per
-// class instead, persistent kernels that pull tiles from device work queues.
-// The autotuner times the configurations of every class on the caller's data,
-// first each class alone and then within the whole graph, and keeps the
-// fastest, or the merged kernels if they are.
+// separately for the estimate and demod kernels).  Once a class's configuration
+// is set, the graph is one two-node branch per class instead, persistent kernels
+// that pull tiles from device work queues.  The autotuner times the
+// configurations of every class on the caller's data, first each class alone and
+// then within the whole graph, and keeps the fastest, or the merged kernels if
+// they are.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -67,6 +67,7 @@ struct rx_batch_s {
   std::vector<int64_t> pf_off;                       // pilot-factor offset of each frame
   std::vector<BatchClass> cls;
   std::vector<BatchGroup> groups;
+  bool merged = true;  // the merged kernels run, else each class's own
   int device = -1;
   int n_cu = 0;
   float2* d_pf = nullptr;
@@ -128,11 +129,6 @@ rx::FrameDesc frame_desc(const rx_batch_s* b, int i) {
   d.N = p.fft_len;
   return d;
 }
-
-bool default_config(const BatchClass& c) {
-  return c.demod_waves == 4 && c.est_jobs == 4 && c.dem_sched == 0 && c.est_sched == 0;
-}
-bool merged(const rx_batch_s* b) { return std::all_of(b->cls.begin(), b->cls.end(), default_config); }
 
 template <typename T>
 int upload(T** dst, const std::vector<T>& v) {
@@ -331,7 +327,7 @@ int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
   kp.extra = nullptr;
   hipGraphNode_t reset;
   if (hipGraphAddKernelNode(&reset, b->graph, nullptr, 0, &kp) != hipSuccess) return RX_E_HIP;
-  if (merged(b)) {
+  if (b->merged) {
     rx::BatchTwiddles tws{};
     for (const auto& c : b->cls) tws.tw[__builtin_ctz(c.N) - 6] = c.d_tw;
     for (size_t gi = 0; gi < b->groups.size(); gi++) {
@@ -355,7 +351,7 @@ int build_graph(rx_batch_s* b, const rx::BatchIo& io) {
         return RX_E_HIP;
     }
   }
-  for (size_t ci = 0; ci < b->cls.size() && !merged(b); ci++) {
+  for (size_t ci = 0; ci < b->cls.size() && !b->merged; ci++) {
     const BatchClass& c = b->cls[ci];
     KernelArgs ea, da;
     est_args(b, c, ci, io, ea);
@@ -571,6 +567,7 @@ int rx_batch_autotune(rx_batch_t b, const int16_t* iq, float* H, float* xhat, ui
     if (st == RX_OK && hipStreamSynchronize(s) != hipSuccess) st = RX_E_HIP;
   }
   drop_graph(b);
+  b->merged = false;
   // Pass 1: each class alone, its estimate and demod kernels timed separately
   // (minimum over the timed runs: robust to interference); the estimate's
   // jobs and schedule and the demod's workgroup size and schedule are chosen
@@ -681,19 +678,13 @@ int rx_batch_autotune(rx_batch_t b, const int16_t* iq, float* H, float* xhat, ui
       for (int se = 0; se < n_sched; se++) consider(Cfg{shape.w, shape.j, sd, se});
     if (st == RX_OK) st = set(c, best_cfg);
   }
-  // The merged kernels (every class at the default) stay unless the tuned
-  // classes are more than 1 % faster.
-  if (st == RX_OK && !merged(b)) {
-    std::vector<Cfg> tuned;
-    for (const auto& c : b->cls) tuned.push_back(Cfg{c.demod_waves, c.est_jobs, c.dem_sched, c.est_sched});
-    float t_tuned = 0.f, t_merged = 0.f;
-    st = time_whole(&t_tuned);
-    for (auto& c : b->cls)
-      if (st == RX_OK) st = set(c, Cfg{4, 4, 0, 0});
-    if (st == RX_OK) st = time_whole(&t_merged);
-    for (size_t i = 0; i < tuned.size() && st == RX_OK && t_tuned < 0.99f * t_merged; i++)
-      st = set(b->cls[i], tuned[i]);
-  }
+  // The merged kernels take over unless the tuned classes are more than 1 %
+  // faster.
+  float t_tuned = 0.f, t_merged = 0.f;
+  if (st == RX_OK) st = time_whole(&t_tuned);
+  b->merged = true;
+  if (st == RX_OK) st = time_whole(&t_merged);
+  if (st == RX_OK) b->merged = t_tuned >= 0.99f * t_merged;
   drop_graph(b);  // rebuilt for the chosen configurations by the next rx_batch_process
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -705,8 +696,9 @@ int rx_batch_config(rx_batch_t b, int32_t fft_len, int32_t* demod_waves, int32_t
   if (!b) return RX_E_INVALID_ARG;
   for (const auto& c : b->cls)
     if (c.N == fft_len) {
-      if (demod_waves) *demod_waves = c.demod_waves;
-      if (est_jobs) *est_jobs = c.est_jobs;
+      const rx::BatchMerged& k = b->groups.front().k;
+      if (demod_waves) *demod_waves = b->merged ? k.dem_block / 64 : c.demod_waves;
+      if (est_jobs) *est_jobs = b->merged ? k.est_jobs : c.est_jobs;
       return RX_OK;
     }
   return RX_E_INVALID_ARG;
@@ -716,8 +708,8 @@ int rx_batch_schedules(rx_batch_t b, int32_t fft_len, int32_t* dem_sched, int32_
   if (!b) return RX_E_INVALID_ARG;
   for (const auto& c : b->cls)
     if (c.N == fft_len) {
-      if (dem_sched) *dem_sched = c.dem_sched;
-      if (est_sched) *est_sched = c.est_sched;
+      if (dem_sched) *dem_sched = b->merged ? 0 : c.dem_sched;
+      if (est_sched) *est_sched = b->merged ? 0 : c.est_sched;
       return RX_OK;
     }
   return RX_E_INVALID_ARG;
@@ -750,6 +742,8 @@ int rx_batch_set_config(rx_batch_t b, int32_t fft_len, int32_t demod_waves, int3
     c.dem_sched = old[2];
     c.est_sched = old[3];
     (void)configure_class(b, c);
+  } else {
+    b->merged = false;
   }
   return st;
 }

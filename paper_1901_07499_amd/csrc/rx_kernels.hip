@@ -1871,6 +1871,7 @@ BatchMerged merged_of() {
   m.est = reinterpret_cast<const void*>(batch_merged_estimate_kernel<QH, kWavesEst, kJobsMerged>);
   m.dem_block = 64 * W;
   m.est_block = 64 * kWavesEst;
+  m.est_jobs = kJobsMerged;
   merged_length<64, W>(m, 0);
   merged_length<128, W>(m, 1);
   merged_length<256, W>(m, 2);

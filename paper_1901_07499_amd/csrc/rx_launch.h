@@ -101,6 +101,7 @@ const void* batch_reset_func();
 struct BatchMerged {
   const void *dem = nullptr, *est = nullptr;
   int dem_block = 0, est_block = 0;
+  int est_jobs = 0;  // per estimate wavefront
   size_t lds_fft[6] = {}, lds_per_u[6] = {}, est_lds[6] = {};
   int est_ants[6] = {};
 };

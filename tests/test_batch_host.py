@@ -47,6 +47,12 @@ class Batch:
                               deps=[self.lib.stub_dep(i, k) for k in range(v[5])]))
         return nodes
 
+    def config(self, N):
+        v = [ctypes.c_int32() for _ in range(4)]
+        assert self.lib.rx_batch_config(self.h, N, ctypes.byref(v[0]), ctypes.byref(v[1])) == 0
+        assert self.lib.rx_batch_schedules(self.h, N, ctypes.byref(v[2]), ctypes.byref(v[3])) == 0
+        return tuple(x.value for x in v)
+
     def close(self):
         self.lib.rx_batch_destroy(self.h)
 
@@ -78,4 +84,45 @@ def test_launches_hold_fewer_threads_than_the_runtime_takes(lib, frames, T, demo
     assert sum(n["grid"] for n in nodes) == frames * (T - 1)
     for p, n in zip(nodes, nodes[1:]):              # the tiles continue where the launch before ended
         assert n["tiles"] == p["tiles"] + 8 * p["grid"]
+    b.close()
+
+
+def _kinds(nodes):
+    return {"merged" if n["kernel"] in MERGED_DEM or n["kernel"] in MERGED_EST else "class" for n in nodes[1:]}
+
+
+@pytest.mark.parametrize("cfg", [(4, 4, 0, 0), (8, 2, 0, 0)])
+def test_configuration_says_what_runs(lib, cfg):
+    lens = sorted({f[1] for f in MIXED})
+    b = Batch(lib, MIXED)
+    nodes = b.process()
+    assert _kinds(nodes) == {"merged"}
+    waves = {n["block"] // 64 for n in nodes if n["kernel"] in MERGED_DEM}
+    assert {b.config(N)[0] for N in lens} == waves and {b.config(N)[1:] for N in lens} == {(2, 0, 0)}
+    for N in lens:                                  # a configuration that is set is the one that runs
+        assert lib.rx_batch_set_config(b.h, N, *cfg) == 0
+    nodes = b.process()
+    assert _kinds(nodes) == {"class"} and {b.config(N) for N in lens} == {cfg}
+    assert {n["block"] for n in nodes if n["kernel"] in CLASS_DEM} == {64 * cfg[0]}
+    assert lib.rx_batch_set_config(b.h, 64, 3, 4, 0, 0) != 0 and b.config(64) == cfg
+    b.close()
+
+
+def test_set_config_of_one_length_leaves_the_others_at_their_default(lib):
+    b = Batch(lib, MIXED)
+    assert lib.rx_batch_set_config(b.h, 1024, 2, 8, 1, 0) == 0
+    assert _kinds(b.process()) == {"class"}
+    assert b.config(1024) == (2, 8, 1, 0) and b.config(2048) == (4, 4, 0, 0)
+    b.close()
+
+
+@pytest.mark.parametrize("merged_ms,kind", [(1.005, "merged"), (1.02, "class")])
+def test_autotune_keeps_the_faster_kernels(lib, merged_ms, kind):
+    b = Batch(lib, MIXED)
+    lib.stub_set_merged_ms(ctypes.c_float(merged_ms))
+    p = [ctypes.c_void_p(256 * k) for k in (1, 2, 3, 4)]
+    assert lib.rx_batch_autotune(b.h, p[0], p[1], p[2], p[3], None, 2, None) == 0
+    lib.stub_set_merged_ms(ctypes.c_float(1.0))
+    assert _kinds(b.process()) == {kind}
+    assert (b.config(64)[1] == 2) or kind == "class"
     b.close()
