@@ -180,9 +180,7 @@ int build_groups(rx_batch_s* b) {
     if (st == RX_OK) st = upload(&o.d_est, est);
     if (st == RX_OK) st = upload(&o.d_dem, dem);
     if (st != RX_OK) return st;
-    if (o.dem_lds > 65536 && hipFuncSetAttribute(o.k.dem, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)o.dem_lds) != hipSuccess)
-      return RX_E_HIP;
+    if (rx::allow_lds(o.k.dem, o.dem_lds) != hipSuccess) return RX_E_HIP;
   }
   return RX_OK;
 }
@@ -226,12 +224,8 @@ int configure_class(rx_batch_s* b, BatchClass& c) {
     return RX_E_HIP;
   c.est_lds = c.est.lds_fft;
   c.dem_lds = std::max(c.dem.lds_fft, c.dem.lds_per_u * (size_t)c.max_u);
-  for (auto* k : {&c.est, &c.dem}) {
-    const size_t lds = k == &c.est ? c.est_lds : c.dem_lds;
-    if (lds > 65536 &&
-        hipFuncSetAttribute(k->func, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return RX_E_HIP;
-  }
+  if (rx::allow_lds(c.est.func, c.est_lds) != hipSuccess || rx::allow_lds(c.dem.func, c.dem_lds) != hipSuccess)
+    return RX_E_HIP;
   int occ_e = 0, occ_d = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_e, c.est.func, c.est.block, c.est_lds) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_d, c.dem.func, c.dem.block, c.dem_lds) != hipSuccess)

@@ -1397,9 +1397,7 @@ size_t fft_lds_bytes() {
 // Dynamic LDS above 64 KB must be allowed per kernel before launching it.
 template <typename K>
 hipError_t allow_lds(K kernel, size_t bytes) {
-  if (bytes <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
+  return rx::allow_lds(reinterpret_cast<const void*>(kernel), bytes);
 }
 
 // Workgroups of `kernel` (block threads, lds bytes) the current device holds at

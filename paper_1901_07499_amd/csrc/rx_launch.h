@@ -27,6 +27,17 @@ hipError_t launch_mfma_estimate(const LaunchArgs& la, float2* H);
 hipError_t launch_mfma_demod(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits);
 hipError_t launch_mfma_fft(const LaunchArgs& la, float2* Y);
 
+// Lets `kernel` take `bytes` of dynamic LDS.  The allowance belongs to the
+// process, not to the plan or batch that asks, so it is one value for all of
+// them: more than any launch takes (12 bytes per transform slot and subcarrier,
+// at most 8 wavefronts x 1024 points, and the codes: 101 KB), and with the
+// longest twiddle table (15 KB) within the 160 KB.
+constexpr int kLdsAllowed = 128 * 1024;
+inline hipError_t allow_lds(const void* kernel, size_t bytes) {
+  return bytes <= 65536 ? hipSuccess
+                        : hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsAllowed);
+}
+
 hipError_t launch_estimate(const LaunchArgs& la, float2* H);
 hipError_t launch_g(const LaunchArgs& la, const float2* H, float* g);
 // Both combiners: with one user ZF is MRC normalised by the channel energy.

@@ -126,3 +126,17 @@ def test_autotune_keeps_the_faster_kernels(lib, merged_ms, kind):
     assert _kinds(b.process()) == {kind}
     assert (b.config(64)[1] == 2) or kind == "class"
     b.close()
+
+
+def test_lds_allowance_does_not_depend_on_the_batch(lib):
+    # kernels are shared by all batches of the process: a later, smaller batch must not lower what an earlier one needs
+    big = Batch(lib, [(130, 2048, 1200, 4), (130, 64, 62, 4)])
+    dem = [n for n in big.process() if n["kernel"] in MERGED_DEM]
+    assert max(n["lds"] for n in dem) > 65536
+    small = Batch(lib, [(130, 2048, 1200, 4), (130, 64, 50, 4)])
+    small.process()
+    for n in big.process(base=4096):                # rebuilt on other buffers
+        if n["lds"] > 65536:
+            assert n["lds"] <= lib.stub_lds(n["kernel"])
+    big.close()
+    small.close()
