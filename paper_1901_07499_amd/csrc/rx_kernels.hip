@@ -1590,6 +1590,29 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
   return hipErrorInvalidValue;  // not reached: short transforms took the items kernel
 }
 
+// Whether the 6- and 7-register windows of the 128- and 256-point transforms pay.
+// At 3 workgroups per compute unit, 768 places, instead of the 8-register
+// kernel's 512 a call can end on a round that is nearly empty, and the 128-point
+// 7-register kernel spills (12 bytes), so that it gains little but where the call
+// is one round instead of two.  Its time against the 8-register kernel's, 108
+// subcarriers, 48 antennas: 1.15 at 270 workgroups, 0.85 at 600 and 760, 1.14 to
+// 1.16 at 790 to 1020, 0.97 to 1.04 beyond; 16 antennas 0.80 at 540, 1.09 at 1020,
+// 0.91 to 0.99 beyond.  256 points, 220 subcarriers, 48 antennas: 0.96 at 600, 0.86
+// at 760, 1.02 to 1.05 at 790 to 1020 (128 antennas 1.09, 16 antennas 0.95), 0.92 to
+// 0.97 beyond.  The other lengths gain, or lose at most 2.5 % (1024 and 2048 points
+// at up to 512 workgroups).
+template <int N>
+bool narrow_pays(const LaunchArgs& la, int need) {
+  const int64_t items = la.S_call * (la.T - 1);
+  if (items <= kSmallItems) return true;
+  const int wa = demod_waves_per_item(la.A, items, FftShape<N>::F);
+  const int64_t groups = items * wa / (kWavesDemod * FftShape<N>::F);
+  const bool few = la.A < 32;
+  if (N == 128 && need == 7) return (groups > 512 && groups <= 768) || (few && groups > 1024);
+  if (N == 256) return few || groups <= 768 || groups > 1024;
+  return true;
+}
+
 // Register-window tiers: the smallest instantiated QH >= ceil((U/2 + 1) / L).
 // 6 and 7 run 3 wavefronts per SIMD where 8 runs 2: 64 antennas, 600 slots, 700 of
 // 1024 subcarriers 726 us with 8 registers and 670 with 6, 1400 of 2048 1667 and
@@ -1603,9 +1626,10 @@ hipError_t demod_n(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t*
   if (need <= 2) return demod_qh<N, 2>(la, H, xhat, bits);
   if (need <= 4) return demod_qh<N, 4>(la, H, xhat, bits);
   if (need <= 5) return demod_qh<N, 5>(la, H, xhat, bits);
-  if (need <= 6) return demod_qh<N, 6>(la, H, xhat, bits);
+  const bool narrow = narrow_pays<N>(la, need);
+  if (need <= 6 && narrow) return demod_qh<N, 6>(la, H, xhat, bits);
   if constexpr (N <= 256 || N == 1024) {
-    if (need <= 7) return demod_qh<N, 7>(la, H, xhat, bits);
+    if (need <= 7 && narrow) return demod_qh<N, 7>(la, H, xhat, bits);
   }
   if (need <= 8) return demod_qh<N, 8>(la, H, xhat, bits);
   return hipErrorInvalidValue;
