@@ -474,20 +474,35 @@ __device__ __forceinline__ void pack_codes(const uint8_t* codes, int n, int B, u
 }
 
 // Output of one data symbol by the whole workgroup of W wavefronts: sum(d, z,
-// g) gives the sums of subcarrier d; x = equalize(d, z, g), one thread per
+// g) gives the sums of subcarrier d; x = z / g (0 when g = 0), one thread per
 // subcarrier, then the decisions, whose codes meet in LDS (codes: U bytes and
 // 3 of slack, 4-byte aligned) and are packed MSB-first, one thread per four
-// (B/2 bytes).  xrow, brow: the symbol's output rows, or null.
-template <int W, typename SumF, typename EqF>
-__device__ __forceinline__ void finish_symbol(int U, int B, SumF sum, EqF equalize, float2* __restrict__ xrow,
+// (B/2 bytes).  xrow, brow: the symbol's output rows, or null.  ZF: past(d, z, g)
+// is x where g is not at most kZfPlain.
+template <int W, typename SumF, typename PastF>
+__device__ __forceinline__ void finish_symbol(int U, int B, bool zf, SumF sum, PastF past, float2* __restrict__ xrow,
                                               uint8_t* __restrict__ brow, uint8_t* codes) {
+  bool edge = false;
   for (int d = threadIdx.x; d < U; d += 64 * W) {
     float2 zz = make_float2(0.f, 0.f);
     float gg = 0.f;
     sum(d, zz, gg);
-    const float2 x = equalize(d, zz, gg);
+    const float2 x = mrc_equalize(zz, gg);
+    edge = edge || !(gg <= kZfPlain);
     if (xrow) xrow[d] = x;
     codes[d] = (uint8_t)qam_code(x, B);
+  }
+  if (zf && edge) {
+    for (int d = threadIdx.x; d < U; d += 64 * W) {
+      float2 zz = make_float2(0.f, 0.f);
+      float gg = 0.f;
+      sum(d, zz, gg);
+      if (!(gg <= kZfPlain)) {
+        const float2 x = past(d, zz, gg);
+        if (xrow) xrow[d] = x;
+        codes[d] = (uint8_t)qam_code(x, B);
+      }
+    }
   }
   if (!brow) return;  // uniform
   __syncthreads();
@@ -502,13 +517,12 @@ struct SlotView {
   float2* xhat;        // [T-1][U]
   uint8_t* bits;       // [T-1][U*B/8]
   int A, T, CP, U, B;
-  bool zf;
 };
 
 // Demodulate data symbol t of one slot with the W wavefronts of the
 // workgroup.  Uses the dynamic LDS `lds` (exchange buffers, then the
 // reduction rows); every thread of the workgroup must call it.
-template <int N, int QH, int W, int S, bool LL>
+template <int N, int QH, int W, bool ZF, int S, bool LL>
 __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* lds,
                                            const FftTwiddles<N, S, LL>& twr) {
   using Sh = FftShape<N>;
@@ -682,7 +696,7 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
   // rows past the antenna count hold zeros
   const int64_t out_row = t - 1;
   const int rows = min(ROWS, A);
-  finish_symbol<W>(U, B, [&](int d, float2& zz, float& gg) {
+  finish_symbol<W>(U, B, ZF, [&](int d, float2& zz, float& gg) {
     if constexpr (W == 8) {
       sum_in_chains(rows, [&](int w, float2& p, float& q) {
         p = rz[w * U + d];
@@ -694,9 +708,7 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
         gg += rg[w * U + d];
       }
     }
-  }, [&](int d, float2 zz, float gg) {
-    return sv.zf && !(gg <= kZfPlain) ? zf_past_plain(zz, gg, Hs + d, A, U) : mrc_equalize(zz, gg);
-  }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
+  }, [&](int d, float2 zz, float gg) { return zf_past_plain(zz, gg, Hs + d, A, U); }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
   reinterpret_cast<uint8_t*>(rg + ROWS * U));
 }
 
@@ -718,12 +730,14 @@ constexpr bool demod_twiddles_in_lds() {
 template <int N, int QH, int W>
 constexpr int demod_min_waves() { return W == 8 ? 2 : (N == 2048 && QH == 5) || QH == 6 || QH == 7 ? 3 : 1; }
 
-// Uniform slots: one workgroup per (slot, data symbol).
-template <int N, int QH, int W>
+// Uniform slots: one workgroup per (slot, data symbol).  (ZF by an instance of
+// its own: with its epilogue behind a scalar, calls of 260 items of 4 or 8
+// antennas x 1024 points took 0.5 us longer, of 12 and 14.)
+template <int N, int QH, int W, bool ZF>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(demod_min_waves<N, QH, W>())))
 void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int CP, int U, int B,
                   const float2* __restrict__ tw, const float2* __restrict__ H, float2* __restrict__ xhat,
-                  uint8_t* __restrict__ bits, int zf) {
+                  uint8_t* __restrict__ bits) {
   using Tw = FftTwiddles<N, 0, demod_twiddles_in_lds<N, QH, W>()>;
   extern __shared__ float2 lds[];
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
@@ -739,8 +753,7 @@ void demod_kernel(const uint32_t* __restrict__ iq, int64_t S, int A, int T, int 
   sv.xhat = xhat ? xhat + s * Td * (int64_t)U : nullptr;
   sv.bits = bits ? bits + s * Td * (int64_t)(U * B / 8) : nullptr;
   sv.A = A; sv.T = T; sv.CP = CP; sv.U = U; sv.B = B;
-  sv.zf = zf;
-  demod_tile<N, QH, W>(sv, t, lds, twr);
+  demod_tile<N, QH, W, ZF>(sv, t, lds, twr);
 }
 
 // Several (slot, data symbol) items per workgroup, for transforms shorter than
@@ -945,12 +958,11 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
     // subcarrier v = litem * U + d, stepped without a division
     constexpr int kStride = 64 * W;
     const int sq = kStride / U, sr = kStride - sq * U;
-    int litem = threadIdx.x / U, d = threadIdx.x - litem * U;
-    for (int v = threadIdx.x; v < nsub; v += kStride) {
+    auto sums = [&](int litem, int d, float2& zz, float& gg) {
       const int lf = __builtin_ctz(Sh::F) - lfa;  // log2 of the items per wavefront
       const int row0 = (litem >> lf) * Wa * Sh::F + ((litem & (FI - 1)) << lfa);  // wavefront sub 0, slot 0
-      float2 zz = make_float2(0.f, 0.f);
-      float gg = 0.f;
+      zz = make_float2(0.f, 0.f);
+      gg = 0.f;
       if constexpr (SPLIT) {
         sum_in_chains(step, [&](int k, float2& p, float& q) {
           const int r = (row0 + (k >> lfa) * Sh::F + (k & (Fa - 1))) * U + d;
@@ -964,12 +976,15 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
           gg += rg[r];
         }
       }
-      float2 x = mrc_equalize(zz, gg);
-      if (zf && !(gg <= kZfPlain)) {
-        int td = Td;
-        asm volatile("" : "+s"(td));  // a division anew: its reciprocal of Td is not held through the loop above
-        x = zf_past_plain(zz, gg, H + slot_of(item0 + litem, td) * A * U + d, A, U);
-      }
+    };
+    bool edge = false;  // ZF: a channel energy past kZfPlain
+    int litem = threadIdx.x / U, d = threadIdx.x - litem * U;
+    for (int v = threadIdx.x; v < nsub; v += kStride) {
+      float2 zz;
+      float gg;
+      sums(litem, d, zz, gg);
+      const float2 x = mrc_equalize(zz, gg);
+      edge = edge || !(gg <= kZfPlain);
       if (xhat) xhat[item0 * U + v] = x;
       codes[v] = (uint8_t)qam_code(x, B);
       d += sr;
@@ -977,6 +992,21 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
       if (d >= U) {
         d -= U;
         litem++;
+      }
+    }
+    if (zf && edge) {
+      int td = Td;
+      asm volatile("" : "+s"(td));  // a division anew: its reciprocal of Td is not held through the antenna loop
+      for (int v = threadIdx.x; v < nsub; v += kStride) {
+        const int it = v / U, e = v - it * U;
+        float2 zz;
+        float gg;
+        sums(it, e, zz, gg);
+        if (!(gg <= kZfPlain)) {
+          const float2 x = zf_past_plain(zz, gg, H + slot_of(item0 + it, td) * A * U + e, A, U);
+          if (xhat) xhat[item0 * U + v] = x;
+          codes[v] = (uint8_t)qam_code(x, B);
+        }
       }
     }
   }
@@ -993,13 +1023,9 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 // estimate kernel's, but for where the compiler fuses a product and a sum) and
 // goes on to the antenna's data symbol, so no second kernel waits for an
 // estimate in memory; the pilot's transform is repeated for every data symbol,
-// on compute units that would idle.  Hout, if not null, receives the estimate (NB == 1).
-// With NB > 1 the groups' sums go to zp, gp and small_finish_kernel adds them in
-// group order.
-__device__ __forceinline__ float2 small_equalize(float2 z, float g, int zf) {
-  return zf && !(g <= kZfPlain) ? zf_past_plain(z, g, g > 0.f) : mrc_equalize(z, g);
-}
-
+// on compute units that would idle.  Hout, if not null, receives the estimate
+// (NB == 1).  With NB > 1 the groups' sums go to zp, gp and small_finish_kernel
+// adds them in group order.
 template <int N, int QH, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void small_kernel(
     const uint32_t* __restrict__ iq, int A, int T, int CP, int U, int B, const float2* __restrict__ tw,
@@ -1105,7 +1131,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
     }, zz, gg);
   };
   if (NB == 1) {
-    finish_symbol<W>(U, B, sum, [&](int, float2 zz, float gg) { return small_equalize(zz, gg, zf); },
+    finish_symbol<W>(U, B, zf, sum, [&](int, float2 zz, float gg) { return zf_past_plain(zz, gg, gg > 0.f); },
                      xhat ? xhat + item * U : nullptr,
                      bits ? bits + item * (int64_t)(U * B / 8) : nullptr, reinterpret_cast<uint8_t*>(rg + rows * U));
   } else {
@@ -1130,12 +1156,13 @@ __global__ __launch_bounds__(64 * kWavesFinish) void small_finish_kernel(const f
   __shared__ uint32_t codes[kSeg / 4 + 1];
   const int segs = (U + kSeg - 1) / kSeg, d0 = blockIdx.x % segs * kSeg;
   const int64_t item = blockIdx.x / segs, s = item / Td;
-  finish_symbol<kWavesFinish>(min(kSeg, U - d0), B, [&](int d, float2& zz, float& gg) {
+  finish_symbol<kWavesFinish>(min(kSeg, U - d0), B, zf, [&](int d, float2& zz, float& gg) {
     sum_in_chains(NB, [&](int b, float2& p, float& q) {
       p = zp[(item * NB + b) * U + d0 + d];
       q = gp[(s * NB + b) * U + d0 + d];
     }, zz, gg);
-  }, [&](int, float2 zz, float gg) { return small_equalize(zz, gg, zf); }, xhat ? xhat + item * U + d0 : nullptr, bits ? bits + (item * U + d0) * B / 8 : nullptr,
+  }, [&](int, float2 zz, float gg) { return zf_past_plain(zz, gg, gg > 0.f); },
+  xhat ? xhat + item * U + d0 : nullptr, bits ? bits + (item * U + d0) * B / 8 : nullptr,
   reinterpret_cast<uint8_t*>(codes));
 }
 
@@ -1218,8 +1245,7 @@ __global__ __launch_bounds__(64 * W) void batch_demod_kernel(const FrameDesc* __
     sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
     sv.bits = io.bits ? io.bits + d.b_off : nullptr;
     sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
-    sv.zf = false;
-    demod_tile<N, QH, W>(sv, 1 + tile - d.dem_tile0, lds, twr);
+    demod_tile<N, QH, W, false>(sv, 1 + tile - d.dem_tile0, lds, twr);
     __syncthreads();  // outputs written and LDS free before the next tile
     done_index = d.index;
     done_last = d.T - 2;  // the frame's last data symbol completes it
@@ -1269,8 +1295,7 @@ __device__ __forceinline__ void batch_demod_length(const FrameDesc& d, const Bat
   sv.xhat = io.xhat ? io.xhat + d.x_off : nullptr;
   sv.bits = io.bits ? io.bits + d.b_off : nullptr;
   sv.A = d.A; sv.T = d.T; sv.CP = d.CP; sv.U = d.U; sv.B = d.B;
-  sv.zf = false;
-  demod_tile<N, QH, W>(sv, t, lds, twr);
+  demod_tile<N, QH, W, false>(sv, t, lds, twr);
 }
 
 template <int QH, int W>
@@ -1532,14 +1557,19 @@ size_t rows_lds(size_t exchange, int rows, int U) {
 }
 
 // demod_kernel with W wavefronts.
-template <int N, int QH, int W>
+template <int N, int QH, int W, bool ZF>
 hipError_t demod_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
   const size_t lds = rows_lds(fft_lds_bytes<N, W>(), transforms_per_group<N, W>(), la.U);
-  hipError_t e = allow_lds(demod_kernel<N, QH, W>, lds);
+  hipError_t e = allow_lds(demod_kernel<N, QH, W, ZF>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((demod_kernel<N, QH, W>), dim3((unsigned)(la.S * (la.T - 1))), dim3(64 * W), lds, la.stream,
-                     la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits, (int)la.zf);
+  hipLaunchKernelGGL((demod_kernel<N, QH, W, ZF>), dim3((unsigned)(la.S * (la.T - 1))), dim3(64 * W), lds, la.stream,
+                     la.iq, la.S, la.A, la.T, la.CP, la.U, la.B, la.tw, H, xhat, bits);
   return hipGetLastError();
+}
+
+template <int N, int QH, int W>
+hipError_t demod_launch(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t* bits) {
+  return la.zf ? demod_launch<N, QH, W, true>(la, H, xhat, bits) : demod_launch<N, QH, W, false>(la, H, xhat, bits);
 }
 
 // Items (slot, data symbol) up to which a call is small: one 8-wavefront
