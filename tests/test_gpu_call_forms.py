@@ -32,10 +32,11 @@ def _noalloc(rx, plan, iq, want_xhat=True, want_bits=True):
 
 
 # one group of antennas; several groups (subcarriers that end inside and at the end of a finishing workgroup's 256); the
-# two kernels with 8 wavefronts; a call past the small ones
+# two kernels with 8 wavefronts; a call past the small ones; as many antennas as 4 wavefronts transform, and one more
 @pytest.mark.parametrize("A,N,U,T,S", [(8, 64, 52, 11, 1), (17, 512, 300, 3, 1), (64, 1024, 600, 14, 1),
                                        (64, 1024, 512, 6, 2), (41, 2048, 1200, 5, 1), (24, 1024, 600, 14, 2),
-                                       (12, 256, 180, 8, 60)])
+                                       (12, 256, 180, 8, 60), (1, 2048, 1200, 5, 2), (2, 2048, 1700, 3, 1),
+                                       (3, 2048, 1200, 3, 1)])
 @pytest.mark.parametrize("zf,bits", [(0, 2), (0, 4), (1, 4), (0, 6), (1, 2)])
 def test_forms_of_a_call(rx, A, N, U, T, S, zf, bits):
     cfg = C2.replace(n_ant=A, fft_len=N, cp_len=N // 16 + 1, n_used=U, n_sym=T, bits_per_sym=bits, n_slots=S)
