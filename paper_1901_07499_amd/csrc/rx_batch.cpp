@@ -147,9 +147,9 @@ int build_groups(rx_batch_s* b) {
   // better (12 per compute unit against 8): 8 where the longest tile takes about
   // as long as a compute unit's share of all tiles and is more than one round of
   // an 8-wavefront workgroup's transforms.  Mixed frames of up to 128 antennas x
-  // 2048 points, us with 8 and with 4: 16 frames 141 and 182, 64 frames 147 and
-  // 192, 100 frames 162 and 198 (share 0.9 of the longest tile), 160 frames 225
-  // and 211 (1.5), 256 frames 380 and 272.
+  // 2048 points, us with 8 and with 4: 16 frames 132 and 168, 64 frames 139 and
+  // 176, 100 frames 165 and 184 (share 1.02 of the longest tile), 128 frames 204
+  // and 192 (1.30), 160 frames 243 and 200, 256 frames 402 and 273.
   int64_t total = 0, longest = 0;
   for (int i : order) {
     total += cost(i) * (b->p[i].n_sym - 1);

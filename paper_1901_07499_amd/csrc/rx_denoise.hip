@@ -153,7 +153,7 @@ __device__ __forceinline__ void store_unit(bfbits* __restrict__ Y, int idx, cons
 // of one channel, two make a 16-byte piece, and the four groups of a wavefront
 // store 64 bytes of each of 16 channels, where the product's own registers
 // hold one position of 8 channels (2 bytes a store; the training forward of
-// 1024 rows took 110 us with those, 95 with these).
+// 1024 rows took 104 us with those, 95 with these).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_channels(const bfbits* X, int base, int t0, int U, bfbits* __restrict__ G,
                                                int64_t UP) {
@@ -534,8 +534,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const bfbits* d4r = io.D4 + row * 2 * UP;
     for (int t0 = 0; t0 < U; t0 += TO) {
       // the tile's ReLU masks, requested here for the three layers: read at
-      // their use they cost a memory latency per unit (1024 rows: 150 us; with
-      // the masks ahead and two units at a time, 95)
+      // their use they cost a memory latency per unit (1024 rows: 143 us; with
+      // the masks ahead and two units at a time, 93)
       uint32_t mk[3][4];
       const uint32_t* const M[3] = {io.M3 + row * UP, io.M2 + row * UP, io.M1 + row * UP};
 #pragma unroll
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 // channels), all taps and output channels, so an operand read serves as many
 // products as it can; the two halves of the positions meet in LDS at the end.
 // Bound: reading the deltas and activations once, 0.32 GB for 1024 rows of 1200
-// (60 us at the rate of a large copy); 134 us, 288 with 64-position chunks
+// (60 us at the rate of a large copy); 142 us, 286 with 64-position chunks
 // loaded between their barriers and the bias summed by one thread per channel.
 constexpr int CHUNK = 128, DT_RS = 136, XT_RS = 152;
 
@@ -901,7 +901,7 @@ __device__ __forceinline__ float2 normal_pair(uint64_t wa, uint64_t wb) {
 // product of signed frequency and delay modulo N, a power of two, so a mask of
 // a 32-bit product (|f| < 1024, delay < 2048); as a 64-bit remainder it took
 // most of the kernel.  A Philox block gives two normals: one thread draws
-// both.  1024 rows of 1200 subcarriers, 8 to 24 taps: 125 -> 27 us.
+// both.  1024 rows of 1200 subcarriers, 8 to 24 taps: 123 -> 27 us.
 __global__ __launch_bounds__(kBlock) void dn_gen_kernel(GenArgs g, uint64_t seed, int64_t first_row, int64_t rows,
                                                         float2* __restrict__ Htrue, float2* __restrict__ Hls) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -708,7 +708,8 @@ __device__ __forceinline__ void demod_tile(const SlotView& sv, int t, float2* ld
         gg += rg[w * U + d];
       }
     }
-  }, [&](int d, float2 zz, float gg) { return zf_past_plain(zz, gg, Hs + d, A, U); }, sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
+  }, [&](int d, float2 zz, float gg) { return zf_past_plain(zz, gg, Hs + d, A, U); },
+  sv.xhat ? sv.xhat + out_row * U : nullptr, sv.bits ? sv.bits + out_row * (U * B / 8) : nullptr,
   reinterpret_cast<uint8_t*>(rg + ROWS * U));
 }
 
@@ -1052,7 +1053,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) voi
   El el;
   el.init(li, U, pf);
   // last-pass twiddles in the LDS table where the widest window needs the
-  // registers
+  // registers (at 128 and 256 points it spills 6 and 8 VGPRs without)
   using Tw = FftTwiddles<N, 0, (QH == 8 && N >= 512)>;
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
   Tw twr;

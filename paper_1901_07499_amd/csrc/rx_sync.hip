@@ -82,7 +82,7 @@ __device__ __forceinline__ Best block_best(Best b, Best* sh) {
   return b;
 }
 
-// Bound: with one antenna per workgroup, staging: 1359 samples for 255 chips,
+// Bound: with one antenna per workgroup, staging: 1344 samples for 255 chips,
 // then 20 products per wavefront.  17 344 candidates, 64 antennas, 255 chips:
 // 7.2 us, where 2-way 16-bit dot products, a sliding window of samples in
 // registers, took 21.6 (their instruction rate the bound).
