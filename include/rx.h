@@ -163,11 +163,11 @@ int rx_process_frame(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* 
  * GPU the library runs on, held until the process ends, takes the place of the
  * workspace, and the slots go through in chunks whose estimates fit it (the
  * kernels are chosen for the whole call; xhat and bits are those of
- * rx_process_frame without H bit for bit).  One slot's
- * estimate, A*U*8 bytes, must fit, else RX_E_SCRATCH.  Every call on a GPU
- * shares that GPU's array: calls that overlap on one GPU (different streams,
- * or host threads) race and must be serialised by the caller.  The array
- * needs no clearing (a chunk reads only what it has written).
+ * rx_process_frame without H bit for bit).  One slot's estimate, A*U*8 bytes,
+ * must fit, else RX_E_SCRATCH.  Every call on a GPU shares that GPU's array:
+ * calls that overlap on one GPU (different streams, or host threads) race and
+ * must be serialised by the caller.  The array needs no clearing (a chunk reads
+ * only what it has written).
  * xhat and bits optional but not both NULL. */
 #define RX_NOALLOC_SCRATCH_BYTES (64u << 20)
 int rx_process_frame_noalloc(rx_plan_t plan, const int16_t* iq, int64_t n_slots, float* xhat, uint8_t* bits,
@@ -241,16 +241,17 @@ int rx_batch_config(rx_batch_t batch, int32_t fft_len, int32_t* demod_waves, int
 
 /* Radix schedules in use for the class of FFT length fft_len: of the demod
  * kernel's transforms and of the estimate kernel's (indices as in
- * rx_fft_radices; 0 in the kernels over all lengths).  RX_E_INVALID_ARG if the batch has no such class. */
+ * rx_fft_radices; 0 in the kernels over all lengths).  RX_E_INVALID_ARG if the
+ * batch has no such class. */
 int rx_batch_schedules(rx_batch_t batch, int32_t fft_len, int32_t* dem_sched, int32_t* est_sched);
 
 /* Set the configuration of the class of FFT length fft_len instead of tuning
  * it: demod_waves and est_jobs in {2, 4, 8}, schedules below the count
  * rx_fft_radices accepts for fft_len.  The batch's current device only;
  * RX_E_INVALID_ARG for anything else (the configuration is then unchanged).
- * From then on every length runs its own kernels, a length never set those of
- * 4 wavefronts, 4 jobs and schedules 0.  The next rx_batch_process rebuilds its
- * graph. */
+ * From then on every length runs its own kernels, a length neither set nor tuned
+ * those of 4 wavefronts, 4 jobs and schedules 0.  The next rx_batch_process
+ * rebuilds its graph. */
 int rx_batch_set_config(rx_batch_t batch, int32_t fft_len, int32_t demod_waves, int32_t est_jobs,
                         int32_t dem_sched, int32_t est_sched);
 

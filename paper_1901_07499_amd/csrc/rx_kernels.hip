@@ -922,11 +922,11 @@ void demod_items_kernel(const uint32_t* __restrict__ iq, int64_t S, int A,
 
   // The workgroup's items are consecutive, so their x-hat rows and bit rows
   // are contiguous.  x-hat and the decision codes (to LDS) come straight from
-  // the registers when one transform slot holds an item (for ZF too, its rare
-  // look at the channel would cost the loop above a register); otherwise every slot's
-  // partial sums go to its LDS row and one thread per subcarrier sums the
-  // item's Wa Fa rows in a fixed order.  Then one thread per
-  // four codes packs the bits.
+  // the registers when one transform slot holds an item (MRC: ZF's rare look at
+  // the channel here would cost the loop above a register); otherwise every
+  // slot's partial sums go to its LDS row and one thread per subcarrier sums the
+  // item's Wa Fa rows in a fixed order.  Then one thread per four codes packs the
+  // bits.
   constexpr int ROWS = W * Sh::F;
   const int nitems = (int)min((int64_t)IPW, items - item0);  // the last workgroup may hold fewer
   const int nsub = nitems * U;
@@ -1590,7 +1590,8 @@ hipError_t demod_qh(const LaunchArgs& la, const float2* H, float2* xhat, uint8_t
   // (the rule looks at the whole call's slots: a call that goes through in
   // chunks sums in one order)
   // (two-wavefront transforms meet at the workgroup's barriers, so one or two
-  // antennas take no wavefronts that idle: 13.0 us instead of 13.8)
+  // antennas take no wavefronts that idle: one antenna, 13 items, estimate and
+  // demod 13.0 us instead of 13.8)
   const bool fits_4 = Sh::WPT > 1 && la.A <= transforms_per_group<N, kWavesDemod>();
   if (la.S_call * (la.T - 1) <= kSmallItems && !fits_4) return demod_launch<N, QH, kWavesSmall>(la, H, xhat, bits);
   if constexpr (Sh::WPT == 1) {
