@@ -146,17 +146,18 @@ __device__ __forceinline__ void estimate_job(float2 (&v)[FftShape<N>::P], const 
   exchange_fence<N>();  // this job's LDS reads precede the next job's writes
 }
 
-// LS estimate of one slot's antennas a_wg .. a_wg + TPW*J - 1: transform slot
-// ts = tid / L of the workgroup takes antennas a_wg + ts + j*TPW, j < J, the
+// LS estimate of one slot's antennas a_wg .. a_wg + TPW*jobs - 1: transform slot
+// ts = tid / L of the workgroup takes antennas a_wg + ts + j*TPW, j < jobs, the
 // next job's samples requested before the current transform.  slot_iq: the
 // slot's samples [T][A][CP+N]; Hs: its estimate [A][U].  The loop bound is
 // uniform over whoever shares an exchange fence (the wavefront, or the
 // workgroup for two-wavefront transforms): a transform whose antenna is past
 // A transforms a valid antenna's samples and stores nothing.
-template <int N, int W, int J, int QH, bool COMB, int S, bool LL>
+template <int N, int W, int QH, bool COMB, int S, bool LL>
 __device__ __forceinline__ void estimate_tile(const uint32_t* __restrict__ slot_iq, int A, int CP, int U,
                                               const float2* __restrict__ pf, float2* __restrict__ Hs,
-                                              int a_wg, float2* lds, const FftTwiddles<N, S, LL>& twr, int ps) {
+                                              int a_wg, int jobs, float2* lds, const FftTwiddles<N, S, LL>& twr,
+                                              int ps) {
   using Sh = FftShape<N>;
   constexpr int TPW = transforms_per_group<N, W>();
   const int li = threadIdx.x % Sh::L, ts = threadIdx.x / Sh::L;
@@ -174,13 +175,13 @@ __device__ __forceinline__ void estimate_tile(const uint32_t* __restrict__ slot_
   uint32_t nxt[Sh::P];
   load_symbol<N>(nxt, rec_of(a_wg + ts, a_lead), li, a_wg + ts < A);
 #pragma unroll 1
-  for (int j = 0; j < J; j++) {
+  for (int j = 0; j < jobs; j++) {
     const int lead = a_lead + j * TPW;
     if (lead >= A) break;
     const int a = a_wg + ts + j * TPW;
     float2 v[Sh::P];
     unpack_symbol<N>(v, nxt);
-    if (j + 1 < J && lead + TPW < A) load_symbol<N>(nxt, rec_of(a + TPW, lead + TPW), li, a + TPW < A);
+    if (j + 1 < jobs && lead + TPW < A) load_symbol<N>(nxt, rec_of(a + TPW, lead + TPW), li, a + TPW < A);
     estimate_job<N, S, LL, QH, COMB>(v, el, buf, li, twr, a < A ? Hs + (int64_t)a * U : nullptr, U, ps);
   }
 }
@@ -196,7 +197,7 @@ __device__ __forceinline__ void tile_setup(FftTwiddles<N, S, LL>& twr, float2* t
   twr.load(tw, threadIdx.x % FftShape<N>::L, twtab);
 }
 
-// Uniform slots: workgroup = (slot, group of W*F*J antennas).
+// Uniform slots: workgroup = (slot, group of W*F*jobs antennas).
 // Last-pass twiddles of the estimate kernels: in VGPRs where the kernel runs
 // 2 wavefronts per SIMD either way (N >= 1024 in the workgroup grid below;
 // every batch kernel), in the LDS table where VGPRs would cost a wavefront
@@ -210,12 +211,12 @@ constexpr bool estimate_twiddles_in_lds() { return N == 512; }
 template <int N, int QH, bool COMB>
 constexpr int estimate_min_waves() { return N == 2048 && QH <= 5 && !COMB ? 3 : 1; }
 
-template <int N, int W, int J, int QH, bool COMB>
+template <int N, int W, int QH, bool COMB>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(estimate_min_waves<N, QH, COMB>())))
 void estimate_kernel(const uint32_t* __restrict__ iq, int A, int T, int CP,
                                                           int U, const float2* __restrict__ tw,
                                                           const float2* __restrict__ pf, float2* __restrict__ H,
-                                                          int blocks_per_slot, int ps) {
+                                                          int blocks_per_slot, int jobs, int ps) {
   using Tw = FftTwiddles<N, 0, estimate_twiddles_in_lds<N>()>;
   extern __shared__ float2 lds[];
   __shared__ float2 twtab[Tw::kLdsFloat2 > 0 ? Tw::kLdsFloat2 : 1];
@@ -223,9 +224,9 @@ void estimate_kernel(const uint32_t* __restrict__ iq, int A, int T, int CP,
   tile_setup(twr, twtab, tw);
   const int64_t s = blockIdx.x / blocks_per_slot;
   const int blk = blockIdx.x % blocks_per_slot;
-  const int a_wg = blk * (transforms_per_group<N, W>() * J);
-  estimate_tile<N, W, J, QH, COMB>(iq + s * T * (int64_t)A * (N + CP), A, CP, U, pf, H + s * A * (int64_t)U, a_wg,
-                                   lds, twr, ps);
+  const int a_wg = blk * transforms_per_group<N, W>() * jobs;
+  estimate_tile<N, W, QH, COMB>(iq + s * T * (int64_t)A * (N + CP), A, CP, U, pf, H + s * A * (int64_t)U, a_wg, jobs,
+                                lds, twr, ps);
 }
 
 // Staged sample loads for transforms of at most 8 lanes (F >= 8 per
@@ -1213,7 +1214,7 @@ __global__ __launch_bounds__(64 * W) void batch_estimate_kernel(const FrameDesc*
     if (tile >= n_tiles) break;
     const FrameDesc d = fd[frame];
     const int a_wg = (tile - d.est_tile0) * (transforms_per_group<N, W>() * J);
-    estimate_tile<N, W, J, FftShape<N>::P / 2, false>(io.iq + d.iq_off, d.A, d.CP, d.U, d.pf, io.H + d.h_off, a_wg,
+    estimate_tile<N, W, FftShape<N>::P / 2, false>(io.iq + d.iq_off, d.A, d.CP, d.U, d.pf, io.H + d.h_off, a_wg, J,
                                                      lds, twr, 1);
   }
 }
@@ -1326,7 +1327,7 @@ __device__ __forceinline__ void batch_estimate_length(const FrameDesc& d, const 
                                                       const float2* __restrict__ tw, float2* lds) {
   FftTwiddles<N, 0, false> twr;
   tile_setup<N>(twr, (float2*)nullptr, tw);
-  estimate_tile<N, W, J, QH, false>(io.iq + d.iq_off, d.A, d.CP, d.U, d.pf, io.H + d.h_off, a_wg, lds, twr, 1);
+  estimate_tile<N, W, QH, false>(io.iq + d.iq_off, d.A, d.CP, d.U, d.pf, io.H + d.h_off, a_wg, J, lds, twr, 1);
 }
 
 template <int QH, int W, int J>
@@ -1478,15 +1479,19 @@ hipError_t estimate_nq(const LaunchArgs& la, float2* H) {
     }
     return estimate_grid_launch<N, false, QH, COMB>(la, H);
   }
-  const int per_block = transforms_per_group<N, kWavesEst>() * kJobsEst;  // antennas per workgroup
-  const int bps = (la.A + per_block - 1) / per_block;
+  // antennas per workgroup: one for each transform where such workgroups fit the
+  // compute units at once, 3 per unit, else kJobsEst.  (Estimate and demod of 128
+  // antennas, one slot, 117 and 110 us, 10 slots 133 and 130; at 15 slots, past the
+  // line, 134.5 with kJobsEst and 136 with one.)
+  constexpr int tpg = transforms_per_group<N, kWavesEst>();
+  const int jobs = la.S * ((la.A + tpg - 1) / tpg) <= 3 * 256 ? 1 : kJobsEst;
+  const int bps = (la.A + tpg * jobs - 1) / (tpg * jobs);
   const int64_t grid = la.S * bps;
   const size_t lds = fft_lds_bytes<N, kWavesEst>();
-  hipError_t e = allow_lds(estimate_kernel<N, kWavesEst, kJobsEst, QH, COMB>, lds);
+  hipError_t e = allow_lds(estimate_kernel<N, kWavesEst, QH, COMB>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((estimate_kernel<N, kWavesEst, kJobsEst, QH, COMB>), dim3((unsigned)grid),
-                     dim3(64 * kWavesEst), lds, la.stream, la.iq, la.A, la.T, la.CP, la.U, la.tw, la.pf, H, bps,
-                     la.ps);
+  hipLaunchKernelGGL((estimate_kernel<N, kWavesEst, QH, COMB>), dim3((unsigned)grid), dim3(64 * kWavesEst), lds,
+                     la.stream, la.iq, la.A, la.T, la.CP, la.U, la.tw, la.pf, H, bps, jobs, la.ps);
   return hipGetLastError();
 }
 
@@ -1747,7 +1752,7 @@ hipError_t small_n(const LaunchArgs& la, int NB, float2* scratch, float2* xhat, 
 // workspace leaves out; it takes the same groups, so the same bits).  One slot,
 // this path against the two kernels: 8 antennas x 64 points 6.6 us against 9.1,
 // 64 x 1024 20.8 (16.3 without the estimate behind it) against 25.4, 128 x 512
-// 17.3 against 25.9, 128 x 2048 46.6 against 117.
+// 17.3 against 25.9, 128 x 2048 36.5 against 110.
 int small_groups(const LaunchArgs& la) {
   const int64_t Td = la.T - 1, items = la.S_call * Td;
   if (la.fft_mode != 0 || la.ps > 1 || items > kSmallItems) return 0;

@@ -40,3 +40,20 @@ def test_workspace_holds_the_estimate(rx, A, N, U, T, S, zf, ps):
     # transforms of kernels that round apart: log2(N) half ulps of the largest bin each
     assert ((kept - H).abs() <= 2 * np.log2(N) * 2.0 ** -24 * H.abs().amax()).all()
     assert (ws[need:] == 0xFF).all()
+
+
+@pytest.mark.parametrize("A,S", [(9, 154), (128, 13), (1, 769)])
+def test_estimate_of_2048_points_on_both_sides_of_its_launch_rule(rx, A, S):
+    # S slots take four transforms in a row, S - 1 slots, at most 768 workgroups of two, one
+    print("[case] estimate launch", A, S, flush=True)
+    N, U, T, CP = 2048, 1200, 2, 16
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    iq = torch.randint(-9000, 9001, (S, T, A, CP + N, 2), generator=gen, device="cuda", dtype=torch.int16)
+    plan = rx.Plan(A, N, CP, U, T, 4, np.ones(U))
+    H = plan.estimate(iq)
+    y = iq[:, 0, :, CP:].double()
+    bins = torch.cat([torch.arange(N - U // 2, N), torch.arange(1, U // 2 + 1)]).cuda()
+    ref = torch.view_as_real(torch.fft.fft(torch.complex(y[..., 0], y[..., 1]))[..., bins])
+    assert ((H - ref).abs() <= np.log2(N) * 2.0 ** -24 * ref.abs().amax()).all()
+    for n in (S - 1, 1):
+        assert torch.equal(plan.estimate(iq[:n]), H[:n])
